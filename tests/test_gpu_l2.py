@@ -126,3 +126,26 @@ def test_l2_medium_chain():
     so = P.oracle_summary_sharded(t)
     o = oracle.l2(so["count"], so["sum_ns"], R, S, K, route, off, mem)
     assert_l2_equal(g, o, "medium chain")
+
+
+@pytest.mark.parametrize("size,E,scale", [(7, 2049, 1), (8, 2047, 1), (9, 65, 1), (24, 130, 1), (25, 64, 1),
+                                          (32, 513, 1), (33, 300, 1), (191, 70, 1), (193, 1, 1), (512, 3, 1),
+                                          (8, 65, 2**13), (40, 65, 2**13), (200, 9, 2**13)])
+def test_l2_group_size_edges(size, E, scale):
+    """Group sizes around the batch (8), the means kept between the passes
+    (24 to a wavefront), the small / large boundary (32) and eight wavefronts'
+    keep (192); event counts around the 64-lane and 2,048-id tiles; scale 2^13
+    puts the means of some members beyond 2^32 ns and some sums beyond 2^53
+    (the wide arithmetic) next to narrow ones."""
+    _announce(f"l2 group size {size}, {E} events, scale {scale}")
+    rng = np.random.default_rng(size * 7919 + E)
+    G = 11  # more groups than one workgroup's wavefronts
+    R, S = size * G, 2
+    cnt = rng.integers(0, 4, size=R * S * E).astype(np.uint32)
+    xs = rng.integers(10**5, 10**6, size=R * S * E) * rng.integers(1, 1 + scale, size=R * S * E)
+    cnt[xs > 2**32] *= np.uint32(2**21)
+    sm = xs * cnt.astype(np.int64) + rng.integers(0, 3, size=R * S * E) * (cnt > 3)
+    route = rng.integers(0, 3, size=E).astype(np.uint8)
+    off = np.tile(np.arange(G + 1, dtype=np.int32) * size, (2, 1))
+    mem = np.stack([rng.permutation(R), np.arange(R)]).astype(np.int32)
+    _both(cnt, sm, R, S, E, route, off, mem, f"size {size} E {E} scale {scale}", z_pm=1500)
