@@ -13,7 +13,7 @@
 //                        writes them as aligned 64-byte groups. HBM bound:
 //                        24 B read and 8 B written per event.
 //   kde_route_kernel,    every cell routed once: empty cells written, heavy
-//   kde_lane_order_kernel cells to the workgroup tier, large or wide-grid
+//   kde_order_kernel cells to the workgroup tier, large or wide-grid
 //                        cells to tier 0, the rest to the lane passes in
 //                        cost-class order (grid size x duration count).
 //   kde_lane_kernel<64>, one cell per lane, 64 cells per wavefront (grids of
@@ -114,6 +114,7 @@ struct KdeArgs {
                        // (both are consumed before tier 1 starts)
   uint16_t* lane_key;  // [cells]: route code (a lane pass's cost class, heavy, tier 0, or none)
   uint32_t* lane_cls;  // [2 * 1024]: cells per cost class, then the classes' fill cursors
+  int32_t no_lanes;    // every cell that is not heavy goes to tier 0: no lane passes
   uint32_t theta[64];  // ceil(2^(23 + t/64))
 };
 
@@ -1451,23 +1452,50 @@ __global__ __launch_bounds__(kWave, TIER == 0 ? 4 : 1) void kde_cell_kernel(KdeA
   const int l = lane_id();
   L.th[l] = a.theta[l];
   wave_sync();
+  // Tier 0: the list (final before this kernel starts, its routed part in
+  // descending cost) is dealt out to the wavefronts one cell at a time, so all
+  // get like shares of every cost; from 32 cells per wavefront on the last
+  // quarter is claimed off a queue instead, in shares that shrink to single
+  // cells, which evens out what the wavefronts' speeds differ by. Claims of 64
+  // cells throughout left most wavefronts without work on short lists (1,076
+  // us for 2,048 cells, 100 us dealt out) and a tail of up to 64 cells, about
+  // 1.5 ms, on longer ones; queues alone pay for the claim's and the
+  // summaries' latency at every short claim.
+  uint32_t len0 = 0, at = blockIdx.x, dealt = 0;
+  if constexpr (TIER == 0) {
+    len0 = __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(&a.counters[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const uint32_t each = len0 / gridDim.x;
+    dealt = each < 32 ? len0 : each / 4 * 3 * gridDim.x;
+  }
   while (true) {
-    uint32_t claim = 0;
-    if (l == 0) claim = atomicAdd(&a.counters[TIER == 0 ? 1 : (TIER == 1 ? 3 : 5)], 1u);
-    claim = __builtin_amdgcn_readfirstlane(claim);
     if constexpr (TIER == 0) {
-      const uint32_t len0 = __builtin_amdgcn_readfirstlane(
-          __hip_atomic_load(&a.counters[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      const int64_t i0 = (int64_t)claim * kWave;
-      if (i0 >= (int64_t)len0) break;
-      const int ncells = (int64_t)len0 - i0 < kWave ? (int)((int64_t)len0 - i0) : kWave;
+      // cells at, at + step, ... of the list
+      uint32_t step = gridDim.x;
+      int ncells = 0;
+      if (at < dealt) {
+        const uint32_t left = (dealt - 1 - at) / step + 1;
+        ncells = left < (uint32_t)kWave ? (int)left : kWave;
+      } else {
+        // a share of a quarter of what the queue held when last seen
+        const uint32_t rest = at < len0 ? len0 - at : 0;
+        uint32_t per = rest / (4 * step);
+        per = per < 1 ? 1 : (per > (uint32_t)kWave ? kWave : per);
+        uint32_t claim = 0;
+        if (l == 0) claim = atomicAdd(&a.counters[1], per);
+        claim = __builtin_amdgcn_readfirstlane(claim);
+        if (claim >= len0 - dealt) break;
+        at = dealt + claim;
+        step = 1;
+        ncells = (int)(len0 - at < per ? len0 - at : per);
+      }
       // every lane fetches one listed cell's summary; the wave then walks the
       // cells, loading the next small cell's durations while it works on this one
       CellMeta mine{};
       mine.off = -1;
       int64_t cell = 0;
       if (l < ncells) {
-        cell = a.list2[i0 + l];
+        cell = a.list2[at + (uint32_t)l * step];
         mine = load_meta(a, cell);
       }
       // cur is only ever a copy of nxt, taken once its loads are complete,
@@ -1488,7 +1516,11 @@ __global__ __launch_bounds__(kWave, TIER == 0 ? 4 : 1) void kde_cell_kernel(KdeA
         load_small(a, mn, nxt);
         finish_or_hand_on<TIER>(a, L, (int64_t)readlane64((uint64_t)cell, i), m, cur);
       }
+      if (at < dealt) at = dealt - at > kWave * step ? at + kWave * step : dealt;
     } else {
+      uint32_t claim = 0;
+      if (l == 0) claim = atomicAdd(&a.counters[TIER == 1 ? 3 : 5], 1u);
+      claim = __builtin_amdgcn_readfirstlane(claim);
       const uint32_t len = __builtin_amdgcn_readfirstlane(
           __hip_atomic_load(&a.counters[TIER == 1 ? 2 : 4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       if (claim >= len) break;
@@ -2178,53 +2210,54 @@ __device__ bool lane_cell(const KdeArgs& a, LaneLds<GC>& L, int64_t c, const Cel
 }
 
 // ------------------------------------------------------------------ routing
-// Before the lane passes every cell is routed once, one thread per cell:
+// Before the cell kernels every cell is routed once, one thread per cell:
 // empty cells (and cells whose summary does not match the buckets) are
 // written, heavy cells go to the workgroup tier's list, cells too large for
 // either lane pass to tier 0's list, and the rest to one of the two lane
-// passes, ordered by a cost class. A lane pass runs 64 cells in lockstep, so
-// a wavefront takes as long as its costliest cell, and cells in kernel-id
-// order mix grids of 10 and 64 points and 10 and 255 durations. The class
-// groups cells of similar grid size and duration count, whose loops run
-// similar trip counts: ((G - 1) / 2, (n - 1) / 16) for the first lane pass
+// passes, every list ordered by a cost class. A lane pass runs 64 cells in
+// lockstep, so a wavefront takes as long as its costliest cell, and cells in
+// kernel-id order mix grids of 10 and 64 points and 10 and 255 durations. The
+// class groups cells of similar grid size and duration count, whose loops run
+// similar trip counts: ((64 - G) / 2, (255 - n) / 16) for the first lane pass
 // (G <= 64), kLaneClasses + ((G - 65) / 8, (n - 1) / 16) for the wide pass
-// (65 <= G <= 256). A counting sort over the classes (counts here,
-// positions in kde_lane_order_kernel) lays each lane list out in class
-// order. Each workgroup routes a contiguous range of cells and claims its
-// list ranges with one atomic per list and class.
+// (65 <= G <= 256). The costliest cells come first, so that the last ones
+// claimed are short (first pass 847 -> 788 us, workgroup tier 1,129 -> 872 us
+// on a production step); not in the wide pass, whose widest grids are mostly
+// given up early (328 us as it is, 471 us reversed). A counting sort over the
+// classes (counts here, positions in kde_order_kernel) lays each list out in
+// class order. Each workgroup routes a contiguous range of cells.
 constexpr int kRouteThreads = 512;
 constexpr int kLaneClasses = 512;                          // 32 grid-size x 16 duration-count classes
 constexpr int kWideClasses = 384;                          // 24 x 16 for the wide pass
-constexpr int kClasses = 1024;                             // both, padded to two per thread
-constexpr uint16_t kNoClass = 0xFFFF, kHeavy = 0xFFFE, kTier0 = 0xFFFD;
-constexpr int kOrderPer = 16;  // cells per thread and round in kde_lane_order_kernel
-static_assert(kClasses == 2 * kRouteThreads && kLaneClasses + kWideClasses <= kClasses, "class scan");
+constexpr int kHeavyAt = kLaneClasses + kWideClasses;      // 32 heavy classes, most durations first
+constexpr int kTier0At = kHeavyAt + 32;                    // 96 tier-0 classes, costliest first
+constexpr int kClasses = 1024;                             // all, two per thread
+constexpr uint16_t kNoClass = 0xFFFF;
+constexpr int kOrderPer = 16;  // cells per thread and round in kde_order_kernel
+static_assert(kClasses == 2 * kRouteThreads && kTier0At + 96 == kClasses, "class scan");
+static_assert(kLaneClasses % 128 == 0 && kWideClasses % 128 == 0, "class totals by wavefront");
 static_assert(((kLaneG - 1) >> 1) * 16 + ((kLaneN - 1) >> 4) < kLaneClasses, "lane classes");
 static_assert(((kLaneGW - 65) >> 3) * 16 + ((kLaneN - 1) >> 4) < kWideClasses, "wide classes");
 
-// Route code of a cell from its checked summary: a class, kHeavy, kTier0, or
-// kNoClass (nothing left to do: the empty record is written by the caller).
-__device__ __forceinline__ uint16_t route_code(const CellMeta& m, const uint32_t* th, int sh) {
+// Class of a cell from its checked summary, or kNoClass (nothing left to do:
+// the empty record is written by the caller). Heavy cells are classed by
+// quarter octaves of their duration count and tier-0 cells by n + 2 G, which
+// follows their cost, largest first, so that the cells claimed last are
+// short: in kernel-id order the last claims could hold the largest ones.
+__device__ __forceinline__ uint16_t route_code(const CellMeta& m, const uint32_t* th, int sh, bool no_lanes) {
   if (m.n == 0 || m.off < 0) return kNoClass;
-  if (m.n >= kBlockMin) return kHeavy;
-  if (m.n > (uint32_t)kLaneN) return kTier0;
+  if (m.n >= kBlockMin) {
+    const int e = 31 - __builtin_clz(m.n);
+    const int q = 4 * (e - 11) + (int)((m.n >> (e - 2)) & 3u);
+    return (uint16_t)(kHeavyAt + 31 - (q < 31 ? q : 31));
+  }
   const int G = (grid64((uint64_t)m.mx, th) >> sh) - (grid64((uint64_t)m.mn, th) >> sh) + 1;
-  const int nq = (int)((m.n - 1) >> 4);
-  if (G <= kLaneG) return (uint16_t)(((G - 1) >> 1) * 16 + nq);
-  if (G <= kLaneGW) return (uint16_t)(kLaneClasses + ((G - 65) >> 3) * 16 + nq);
-  return kTier0;
-}
-
-// Index for each lane with pred among the new entries of an LDS list
-// counter: one atomic per wavefront. Called by every lane of the wavefront.
-__device__ __forceinline__ uint32_t wave_append(uint32_t* counter, bool pred) {
-  const uint64_t m = __ballot(pred);
-  if (m == 0) return 0;
-  const int leader = __builtin_ctzll(m);
-  uint32_t base = 0;
-  if (lane_id() == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
-  base = __builtin_amdgcn_readlane(base, leader);
-  return base + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull));
+  if (!no_lanes && m.n <= (uint32_t)kLaneN) {
+    if (G <= kLaneG) return (uint16_t)(((kLaneG - G) >> 1) * 16 + (int)((kLaneN - m.n) >> 4));
+    if (G <= kLaneGW) return (uint16_t)(kLaneClasses + ((G - 65) >> 3) * 16 + (int)((m.n - 1) >> 4));
+  }
+  const int cost = ((int)m.n + 2 * G) >> 5;
+  return (uint16_t)(kTier0At + 95 - (cost < 95 ? cost : 95));
 }
 
 // Contiguous range of cells of workgroup b out of nb.
@@ -2237,67 +2270,54 @@ __device__ __forceinline__ void cell_range(int64_t C, int64_t b, int64_t nb, int
 __global__ __launch_bounds__(kRouteThreads) void kde_route_kernel(KdeArgs a) {
   __shared__ uint32_t hist[kClasses];
   __shared__ uint32_t th[64];
-  __shared__ uint32_t n_heavy, n_tier0, base_heavy, base_tier0;
   const int tid = threadIdx.x;
   if (tid < 64) th[tid] = a.theta[tid];
   hist[tid] = hist[tid + kRouteThreads] = 0;
-  if (tid == 0) n_heavy = n_tier0 = 0;
   __syncthreads();
   const int64_t C = (int64_t)a.n_seg * a.K;
   int64_t c0, c1;
   cell_range(C, blockIdx.x, gridDim.x, c0, c1);
   const int sh = 6 - a.sub_bits;
-  // 1. route codes; empty records; per-workgroup counts
+  // route codes; empty records; per-workgroup counts
   for (int64_t cb = c0; cb < c1; cb += kRouteThreads) {
     const int64_t c = cb + tid;
     uint16_t code = kNoClass;
     if (c < c1) {
       const CellMeta m = load_meta(a, c);
-      code = route_code(m, th, sh);
+      code = route_code(m, th, sh, a.no_lanes != 0);
       if (code == kNoClass) {
         if (m.n != 0) flag(a, ARGUS_DEV_KDE_SUMMARY);
         const uint32_t z[kMaxC] = {0, 0, 0, 0};
         const uint64_t zz[kMaxC] = {0, 0, 0, 0};
         lane_write(a, c, 0, z, zz, zz, 0);
-      } else if (code < kClasses) {
+      } else {
         atomicAdd(&hist[code], 1u);
       }
       a.lane_key[c] = code;
     }
-    wave_append(&n_heavy, code == kHeavy);
-    wave_append(&n_tier0, code == kTier0);
   }
   __syncthreads();
-  // 2. list ranges of this workgroup
-  if (tid == 0) {
-    uint32_t nl = 0, nw = 0;
-    for (int k = 0; k < kLaneClasses; ++k) nl += hist[k];
-    for (int k = kLaneClasses; k < kClasses; ++k) nw += hist[k];
-    if (nl) atomicAdd(&a.counters[12], nl);
-    if (nw) atomicAdd(&a.counters[9], nw);
-    base_heavy = n_heavy ? atomicAdd(&a.counters[11], n_heavy) : 0u;
-    base_tier0 = n_tier0 ? atomicAdd(&a.counters[7], n_tier0) : 0u;
-    n_heavy = n_tier0 = 0;
-  }
-  for (int k = tid; k < kClasses; k += kRouteThreads)
-    if (hist[k]) atomicAdd(&a.lane_cls[k], hist[k]);
-  __syncthreads();
-  // 3. heavy and tier-0 entries (the lane lists are laid out by the next kernel)
-  for (int64_t cb = c0; cb < c1; cb += kRouteThreads) {
-    const int64_t c = cb + tid;
-    const uint16_t code = c < c1 ? a.lane_key[c] : kNoClass;
-    const uint32_t ih = wave_append(&n_heavy, code == kHeavy);
-    if (code == kHeavy) a.list2[C - 1 - (int64_t)(base_heavy + ih)] = (uint32_t)c;
-    const uint32_t i0 = wave_append(&n_tier0, code == kTier0);
-    if (code == kTier0) a.list2[base_tier0 + i0] = (uint32_t)c;
+  // totals per list and class: thread t holds classes 2t and 2t + 1, so the
+  // lists' class ranges are whole wavefronts but for the last two
+  const uint32_t h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
+  if (h0) atomicAdd(&a.lane_cls[2 * tid], h0);
+  if (h1) atomicAdd(&a.lane_cls[2 * tid + 1], h1);
+  const int first = 2 * (tid & ~(kWave - 1));  // first class of this wavefront
+  const uint32_t heavy = first == kHeavyAt && 2 * lane_id() < kTier0At - kHeavyAt ? h0 + h1 : 0u;
+  const uint32_t all = (uint32_t)wave_sum_u64(h0 + h1), nh = (uint32_t)wave_sum_u64(heavy);
+  if (lane_id() == 0) {
+    const int q = first < kLaneClasses ? 12 : (first < kHeavyAt ? 9 : 7);
+    if (all - nh) atomicAdd(&a.counters[q], all - nh);
+    if (nh) atomicAdd(&a.counters[11], nh);
   }
 }
 
-// Positions of the lane passes' cells: class offsets from an exclusive scan
-// of the class counts, a range per class and round claimed with one atomic,
-// ranks inside the round from LDS atomics. First-pass cells of position p
-// go to list1[C - 1 - p], wide cells to list1[p - (first-pass total)].
-__global__ __launch_bounds__(kRouteThreads) void kde_lane_order_kernel(KdeArgs a) {
+// Positions of the listed cells: class offsets from an exclusive scan of the
+// class counts, a range per class and round claimed with one atomic, ranks
+// inside the round from LDS atomics. First-pass cells of position p go to
+// list1[C - 1 - p], wide cells to list1 from the bottom, heavy cells to list2
+// from the top and tier-0 cells to list2 from the bottom.
+__global__ __launch_bounds__(kRouteThreads) void kde_order_kernel(KdeArgs a) {
   __shared__ uint32_t off[kClasses], lcnt[kClasses], lbase[kClasses];
   __shared__ uint32_t wsum[kRouteThreads / kWave];
   const int tid = threadIdx.x, wv = tid / kWave;
@@ -2312,7 +2332,7 @@ __global__ __launch_bounds__(kRouteThreads) void kde_lane_order_kernel(KdeArgs a
     off[2 * tid + 1] = base + v0;
   }
   __syncthreads();
-  const uint32_t n_first = off[kLaneClasses];
+  const uint32_t n_first = off[kLaneClasses], heavy0 = off[kHeavyAt], tier0 = off[kTier0At];
   const int64_t C = (int64_t)a.n_seg * a.K;
   int64_t c0, c1;
   cell_range(C, blockIdx.x, gridDim.x, c0, c1);
@@ -2337,7 +2357,9 @@ __global__ __launch_bounds__(kRouteThreads) void kde_lane_order_kernel(KdeArgs a
       const int64_t c = cb + (int64_t)u * kRouteThreads + tid;
       const int64_t p = (int64_t)off[key[u]] + lbase[key[u]] + rank[u];
       if (key[u] < kLaneClasses) a.list1[C - 1 - p] = (uint32_t)c;
-      else a.list1[p - n_first] = (uint32_t)c;
+      else if (key[u] < kHeavyAt) a.list1[p - n_first] = (uint32_t)c;
+      else if (key[u] < kTier0At) a.list2[C - 1 - (p - heavy0)] = (uint32_t)c;
+      else a.list2[p - tier0] = (uint32_t)c;
     }
     __syncthreads();
   }
@@ -2377,6 +2399,14 @@ __global__ __launch_bounds__(kWave) void kde_lane_kernel(KdeArgs a) {
 }
 
 // ---------------------------------------------------------------- host side
+
+// Up to this many cells, present or not, tier 0 takes the lane passes' cells
+// too: a lane pass takes 225 us however few its cells are, a wavefront's cell
+// about 15 us with 4,096 wavefronts at once. argus_kde at 8,000 / 32,000 /
+// 128,000 / 512,000 cells (500 ids, 30,000 Zipf events per rank-step):
+// 606 / 684 / 795 / 1,463 us with the lane passes, 218 / 298 / 522 / 1,870
+// without.
+constexpr int64_t kFewCells = 1 << 18;
 
 __global__ void kde_pow_table_kernel() {
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2471,6 +2501,7 @@ hipError_t launch_kde(const KdeLaunch& l, hipStream_t st) {
   a.lane_cls = reinterpret_cast<uint32_t*>(ws + off);
   off += al256((size_t)2 * kClasses * 4);
   a.seg_w4 = reinterpret_cast<uint8_t*>(ws + off);
+  a.no_lanes = cells <= kFewCells;
   const uint32_t* th = kde_thresholds();
   for (int t = 0; t < 64; ++t) a.theta[t] = th[t];
 
@@ -2505,13 +2536,15 @@ hipError_t launch_kde(const KdeLaunch& l, hipStream_t st) {
   const int64_t route_wg = (cells + 16383) / 16384 < 512 ? (cells + 16383) / 16384 : 512;
   hipLaunchKernelGGL(kde_route_kernel, dim3((unsigned)route_wg), dim3(kRouteThreads), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(kde_lane_order_kernel, dim3((unsigned)route_wg), dim3(kRouteThreads), 0, st, a);
+  hipLaunchKernelGGL(kde_order_kernel, dim3((unsigned)route_wg), dim3(kRouteThreads), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int64_t chunks = (cells + kWave - 1) / kWave;
-  hipLaunchKernelGGL(kde_lane_kernel<kLaneG>, dim3(chunks < g[4] ? (int)chunks : g[4]), dim3(kWave), 0, st, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(kde_lane_kernel<kLaneGW>, dim3(g[5]), dim3(kWave), 0, st, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!a.no_lanes) {
+    const int64_t chunks = (cells + kWave - 1) / kWave;
+    hipLaunchKernelGGL(kde_lane_kernel<kLaneG>, dim3(chunks < g[4] ? (int)chunks : g[4]), dim3(kWave), 0, st, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(kde_lane_kernel<kLaneGW>, dim3(g[5]), dim3(kWave), 0, st, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(kde_block_kernel, dim3(g[6]), dim3(kBlockThreads), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(kde_cell_kernel<0>, dim3(g[1]), dim3(kWave), 0, st, a);

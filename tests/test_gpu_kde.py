@@ -6,7 +6,8 @@ Cases: the seeded tiny and medium traces (multimodal kernels), parameter
 variants, ragged / corrupted / malformed segments, hand-built groups that
 exercise every filter rule and both LDS paths (cells whose grid, kernel or
 valley list do not fit the fast path are finished by the large-LDS path),
-summaries that do not match the events, segments of 4-byte and 8-byte
+summaries that do not match the events, both routes to the cell kernels
+(with and without the lane passes), segments of 4-byte and 8-byte
 bucket records in one call, a rank-step longer than 2^26 events (the
 scatter's global-load path), the stream array skipped or read, and full-size
 workloads (sampled segments checked against the oracle).
@@ -359,6 +360,39 @@ def test_kde_long_segment_global_path():
     o = oracle.kde(ev_h, K, NS, n_events=len(ev_h["kernel_id"]))
     assert (o["n_clusters"] > 1).sum() > 8  # multimodal kernels are present
     P.assert_kde_equal(got, o, "long rank-step", rows=np.arange(K))
+
+
+@pytest.mark.parametrize("params", [{}, dict(sub_bits=3), dict(frac_pm=0, min_count=1, gap=0)])
+@pytest.mark.parametrize("lanes", [False, True])
+def test_kde_routes(lanes, params):
+    """The same segments on both routes: few cells (no lane passes) and, with
+    empty rank-steps behind them, more than 2^18 cells (lane passes); group
+    sizes and grid widths on both sides of every routing limit (255 / 256 and
+    2,047 / 2,048 durations, 64 / 65 and 256 / 257 grid points), identical
+    durations and absent kernels among them."""
+    _announce(f"kde routes lanes={lanes} {params}")
+    rng = np.random.default_rng(11)
+    K, NS = 96, 4
+    evs = []
+    for seg in range(6):
+        groups = []
+        for i in range(K):
+            n = int(rng.choice([0, 1, 2, 3, 15, 16, 17, 100, 254, 255, 256, 257, 1000, 2047, 2048, 2049, 5000]))
+            octaves = float(rng.choice([0.0, 0.3, 0.98, 1.0, 1.02, 2.0, 3.98, 4.0, 4.03, 9.0]))
+            base = float(rng.uniform(1e3, 1e7))
+            d = base * 2.0 ** (octaves * rng.random(n))
+            if n > 20 and rng.random() < 0.5:  # modes apart
+                d = base * 2.0 ** (octaves * rng.integers(0, 3, n) / 2 + 0.05 * rng.standard_normal(n))
+            groups.append(np.maximum(d, 0).astype(np.uint64))
+        evs.append(_groups_to_events(groups, K, NS, seed=seg))
+    lens = np.array([len(e["kernel_id"]) for e in evs])
+    R = len(evs) if not lanes else (1 << 18) // K + 1
+    off = np.zeros(R + 1, np.int64)
+    off[1:len(evs) + 1] = np.cumsum(lens)
+    off[len(evs) + 1:] = lens.sum()
+    ev = {f: np.concatenate([e[f] for e in evs]) for f in ("kernel_id", "stream", "start_ns", "end_ns")}
+    ev["seg_off"] = off
+    _both(ev, R, 1, K, NS, f"routes lanes={lanes}", **params)
 
 
 @pytest.mark.parametrize("name,n_check", [("production", 96), ("cluster", 48), ("skew", 48)])
