@@ -10,7 +10,8 @@
 //               present ranks, grid bounds lo / hi by 64-bit atomics,
 //               malformed records.
 //   w1_cdf      one lane per rank (64 ranks of one kernel id per wavefront,
-//               eight kernel ids per wavefront): the count-weighted lognormal
+//               eight kernel ids per wavefront; fewer ids and a share of the
+//               grid where there are few cells): the count-weighted lognormal
 //               mixture of Eq. 2 at every grid point, quantised to 16 bits,
 //               into a [S][K][G][R'] workspace (R' = R rounded up to even;
 //               ranks contiguous, so the writes and the next kernel's reads
@@ -19,7 +20,8 @@
 //               whose quantised value is not settled by that bound (within
 //               1e-4 of a step of 2^-16) is recomputed with erfc in double,
 //               the defining formula, so every output equals the erfc form.
-//   w1_score    one workgroup per (step, kernel): for each grid point the
+//   w1_score    (w1_score_pairs up to 1,024 ranks: every pair, see there)
+//               one workgroup per (step, kernel): for each grid point the
 //               exact sums S_a = sum_b |q_a - q_b| over all present ranks
 //               from a counting sort of the 16-bit values in LDS (a
 //               256-bucket histogram, then the 256 bins of each occupied
@@ -64,6 +66,7 @@ constexpr int kPhiSteps = 64;
 constexpr int kPhiN = 2 * 8 * kPhiSteps;  // intervals
 constexpr double kBand = 1e-4;            // in units of 2^-16
 constexpr int kCdfKPerWave = 8;
+constexpr int64_t kCdfWaves = 4096;  // a little more than the CDF kernel's resident wavefronts (three per SIMD)
 
 // per interval i (z from -kPhiZ + i / kPhiSteps), the cubic in t in [0, 1]:
 // c0 + t (c1 + t (c2 + t c3)); filled once per device from the host's erfc / exp
@@ -229,15 +232,21 @@ __device__ __forceinline__ uint32_t quant16(double v) {
   return f >= 65535.0 ? 65535u : (uint32_t)f;
 }
 
-__global__ __launch_bounds__(256) void w1_cdf(W1Args a) {
+// The lanes are ranks; fewer than 64 ranks leave room for those of
+// several kernel ids, of which a wavefront takes k_per_wave (lane groups
+// together) in turn. g_parts workgroups share the grid points.
+__global__ __launch_bounds__(256) void w1_cdf(W1Args a, int k_per_wave, int g_parts) {
   __shared__ double tab[kPhiN * 4];
   for (int i = threadIdx.x; i < kPhiN * 4; i += 256) tab[i] = g_phi_tab[i];
   __syncthreads();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int r = blockIdx.y * 64 + lane, s = blockIdx.z;
-  if (r >= a.R) return;
-  for (int j = 0; j < kCdfKPerWave; ++j) {
-    const int k = (blockIdx.x * 4 + w) * kCdfKPerWave + j;
+  const int pack = a.R < 64 ? 64 / a.R : 1;
+  const int r = a.R < 64 ? lane % a.R : blockIdx.y * 64 + lane;
+  const int s = blockIdx.z / g_parts, part = blockIdx.z % g_parts;
+  const int g_from = (int)((int64_t)a.G * part / g_parts), g_to = (int)((int64_t)a.G * (part + 1) / g_parts);
+  if (r >= a.R || (a.R < 64 && lane >= pack * a.R)) return;
+  for (int j = 0; j < k_per_wave; ++j) {
+    const int k = ((blockIdx.x * 4 + w) * k_per_wave + j) * pack + (a.R < 64 ? lane / a.R : 0);
     if (k >= a.K) break;
     const int64_t sk = (int64_t)s * a.K + k;
     if (!evaluated(a, a.o.n_present[sk])) continue;
@@ -272,8 +281,8 @@ __global__ __launch_bounds__(256) void w1_cdf(W1Args a) {
     }
     const int64_t rs = row_stride(a);
     uint16_t* out = ws_block(a, sk) + r;
-    for (int gb = 0; gb < a.G; gb += 64) {
-      const int gn = a.G - gb < 64 ? a.G - gb : 64;
+    for (int gb = g_from; gb < g_to; gb += 64) {
+      const int gn = g_to - gb < 64 ? g_to - gb : 64;
       uint64_t unsure = 0;
       // the mixture at grid point g: two points per step, so that the two
       // dependent chains of table evaluations overlap
@@ -660,6 +669,201 @@ __global__ __launch_bounds__(NT) void w1_score(W1Args a) {
   }
 }
 
+// Up to kPairRanks ranks: every pair. The grid points' rows of present ranks
+// are staged in LDS, many at a time, packed two values to a word; each
+// thread holds V ranks, each as a word of its value twice, and one v_sad_u16
+// adds the distances to both values of a word that the whole wavefront reads
+// from one address. n^2 / 128 such instructions per grid point and one
+// barrier pair per stage, against eight barriers per point (and a CU's whole
+// LDS) in w1_score. argus_w1, 64 grid points, 2,000 kernels of 64 / 256 / 512 /
+// 1,000 ranks: 2,778 / 3,199 / 3,429 / 4,151 us with w1_score (256 threads),
+// 214 / 441 / 986 / 2,704 us with pairs; n^2 overtakes the sort between 1,024
+// and 2,048 ranks (16,000 cycles per point there, pairs 32,000).
+constexpr int kPairRanks = 1024;
+
+template <int NT, int V>
+__global__ __launch_bounds__(NT) void w1_score_pairs(W1Args a) {
+  static_assert(NT == 256 && V <= 4, "row buffer");
+  constexpr int kStageWords = 8192;  // 32 KB: at least 16 rows
+  static_assert(NT * V <= kPairRanks, "rows");
+  constexpr int NW = NT / 64;
+  __shared__ alignas(16) uint32_t stage[kStageWords];
+  __shared__ double wts[ARGUS_MAX_W1_GRID];
+  __shared__ uint64_t keys[V == 1 ? NT : 1];
+  __shared__ SelShared<2> sel;
+  __shared__ unsigned long long mn_sh, mx_sh, pick[2];
+  __shared__ uint32_t nf_sh, wave_n[V * NW];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t sk = xcd_item(blockIdx.x, gridDim.x);
+  const int s = (int)(sk / a.K), k = (int)(sk % a.K);
+  const uint32_t n = a.o.n_present[sk];
+  double* ws_score = ws_scores(a, sk);
+  uint8_t* ws_flag = ws_flags(a, sk);
+  // thread tid holds ranks tid + j NT
+  if (!evaluated(a, n)) {
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      const int r = tid + j * NT;
+      if (r >= a.R) break;
+      ws_score[r] = 0.0;
+      ws_flag[r] = 0;
+    }
+    if (tid == 0) {
+      a.o.lo_ns[sk] = 0;
+      a.o.hi_ns[sk] = 0;
+      a.o.q1[sk] = a.o.q3[sk] = a.o.fence[sk] = 0.0;
+      a.o.n_flag[sk] = 0;
+    }
+    return;
+  }
+  // place of each present rank among the present ones
+  uint32_t pm = 0;
+  int place[V];
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const int r = tid + j * NT;
+    uint32_t nc = 0;
+    uint64_t tot = 0;
+    const bool here = r < a.R && cell_state(a, cell_of(a, r, s, k), nc, tot) > 0;
+    pm |= (here ? 1u : 0u) << j;
+    const uint64_t b = __ballot(here);
+    place[j] = __popcll(b & ((1ull << lane) - 1));
+    if (lane == 0) wave_n[j * NW + wv] = __popcll(b);
+  }
+  auto present = [&](int j) { return ((pm >> j) & 1u) != 0; };
+  double lnlo, du;
+  grid_of(a, sk, lnlo, du);
+  const int G = a.G;
+  // w_g = (x_{min(g+1,G-1)} - x_{max(g-1,0)}) / 2, x_i = exp(lnlo + i du)
+  for (int g = tid; g < G; g += NT)
+    wts[g] = (exp(lnlo + (double)(g + 1 < G ? g + 1 : G - 1) * du) - exp(lnlo + (double)(g > 0 ? g - 1 : 0) * du)) /
+             2.0;
+  if (tid == 0) {
+    mn_sh = ~0ull;
+    mx_sh = 0;
+    nf_sh = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < V; ++j)
+    for (int i = 0; i < j * NW + wv; ++i) place[j] += (int)wave_n[i];
+
+  // rows of four words, so that a read takes 16 bytes; values past the n
+  // present ones are 0 (each adds the rank's own value, taken off again)
+  const int words = (((int)n + 1) / 2 + 3) & ~3, pad = 2 * words - (int)n;
+  const int rows = kStageWords / words < G ? kStageWords / words : G;
+  const int64_t rs = row_stride(a);
+  const uint16_t* q = ws_block(a, sk);
+  uint16_t* stage16 = reinterpret_cast<uint16_t*>(stage);
+  double acc[V];
+#pragma unroll
+  for (int j = 0; j < V; ++j) acc[j] = 0.0;
+  for (int gb = 0; gb < G; gb += rows) {
+    const int gn = G - gb < rows ? G - gb : rows;
+    for (int i = 0; i < gn; ++i) {
+#pragma unroll
+      for (int j = 0; j < V; ++j)
+        if (present(j)) stage16[2 * words * i + place[j]] = q[(int64_t)(gb + i) * rs + tid + j * NT];
+    }
+    for (int i = tid; i < gn * pad; i += NT) stage16[2 * words * (i / pad) + (int)n + i % pad] = 0;
+    __syncthreads();
+    for (int i = 0; i < gn; ++i) {
+      const uint4* row = reinterpret_cast<const uint4*>(stage + words * i);
+      uint32_t own[V], S[V];
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const uint32_t v = present(j) ? stage16[2 * words * i + place[j]] : 0u;
+        own[j] = v | (v << 16);
+        S[j] = 0u - (uint32_t)pad * v;
+      }
+#pragma unroll 4
+      for (int b = 0; b < words / 4; ++b) {
+        const uint4 w = row[b];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          S[j] = __builtin_amdgcn_sad_u16(own[j], w.x, S[j]);
+          S[j] = __builtin_amdgcn_sad_u16(own[j], w.y, S[j]);
+          S[j] = __builtin_amdgcn_sad_u16(own[j], w.z, S[j]);
+          S[j] = __builtin_amdgcn_sad_u16(own[j], w.w, S[j]);
+        }
+      }
+      const double wg = wts[gb + i];
+#pragma unroll
+      for (int j = 0; j < V; ++j) acc[j] += wg * (double)S[j];
+    }
+    __syncthreads();
+  }
+
+  const double norm = 65536.0 * (double)(n - 1);
+  const uint32_t nm1 = n - 1;
+  const uint32_t ranks[2] = {nm1 / 4, (uint32_t)((3ull * nm1) / 4)};
+  uint64_t key[V];
+#pragma unroll
+  for (int j = 0; j < V; ++j) key[j] = (uint64_t)__double_as_longlong(acc[j] / norm);
+  double a1, a3;
+  if constexpr (V == 1) {
+    // few scores: each one's place by counting (ties by rank)
+    if (present(0)) keys[place[0]] = key[0];
+    __syncthreads();
+    if (present(0)) {
+      uint32_t before = 0;
+      for (int i = 0; i < (int)n; ++i) before += keys[i] < key[0] || (keys[i] == key[0] && i < place[0]) ? 1u : 0u;
+      if (before == ranks[0]) pick[0] = key[0];
+      if (before == ranks[1]) pick[1] = key[0];
+    }
+    __syncthreads();
+    a1 = __longlong_as_double((long long)pick[0]);
+    a3 = __longlong_as_double((long long)pick[1]);
+  } else {
+    unsigned long long mn = ~0ull, mx = 0;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      if (!present(j)) continue;
+      mn = key[j] < mn ? key[j] : mn;
+      mx = key[j] > mx ? key[j] : mx;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const unsigned long long x = __shfl_xor(mn, o, 64), y = __shfl_xor(mx, o, 64);
+      mn = x < mn ? x : mn;
+      mx = y > mx ? y : mx;
+    }
+    if (lane == 0) {
+      atomicMin(&mn_sh, mn);
+      atomicMax(&mx_sh, mx);
+    }
+    __syncthreads();
+    const uint64_t kmin = mn_sh, kmax = mx_sh;
+    uint64_t off[V], qs[2];
+#pragma unroll
+    for (int j = 0; j < V; ++j) off[j] = present(j) ? key[j] - kmin : 0;
+    select_ranks<NT, V, 2>(off, (uint64_t)pm, kmax - kmin, ranks, qs, sel);
+    a1 = __longlong_as_double((long long)(kmin + qs[0]));
+    a3 = __longlong_as_double((long long)(kmin + qs[1]));
+  }
+  const double fence = a3 + (double)a.alpha_pm * (a3 - a1) / 1000.0;
+  uint32_t nf = 0;
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const int r = tid + j * NT;
+    if (r >= a.R) break;
+    const double sc = __longlong_as_double((long long)key[j]);
+    const bool f = present(j) && sc > fence;
+    nf += f ? 1u : 0u;
+    ws_score[r] = present(j) ? sc : 0.0;
+    ws_flag[r] = f ? 1 : 0;
+  }
+  for (int o = 32; o > 0; o >>= 1) nf += __shfl_xor(nf, o, 64);
+  if (lane == 0 && nf) atomicAdd(&nf_sh, nf);
+  lds_barrier();
+  if (tid == 0) {
+    a.o.lo_ns[sk] = a.o.lo_ns[sk] < 1 ? 1 : a.o.lo_ns[sk];
+    a.o.q1[sk] = a1;
+    a.o.q3[sk] = a3;
+    a.o.fence[sk] = fence;
+    a.o.n_flag[sk] = nf_sh;
+  }
+}
+
 // ------------------------------------------------------------------ out
 // The scores and flags of the workspace blocks ([step, kernel][rank]) into
 // the [rank][step][kernel] outputs, through 64 x 64 LDS tiles so that both
@@ -746,15 +950,28 @@ hipError_t launch_w1(const W1Launch& l, hipStream_t st) {
   hipLaunchKernelGGL(w1_bounds, dim3((l.K + 63) / 64, (l.R + 63) / 64, l.S), dim3(256), 0, st, wa);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(w1_cdf, dim3((l.K + 4 * kCdfKPerWave - 1) / (4 * kCdfKPerWave), (l.R + 63) / 64, l.S), dim3(256),
-                     0, st, wa);
+  {
+    // Eight kernel ids per wavefront read neighbouring cluster records
+    // together; where that leaves fewer than kCdfWaves wavefronts, first the
+    // ids and then the grid points (at least eight each) go to more of them.
+    const int pack = l.R < 64 ? 64 / l.R : 1;
+    const int64_t rows = (int64_t)((l.R + 63) / 64) * l.S, groups = (l.K + pack - 1) / pack;
+    int per = kCdfKPerWave, parts = 1;
+    while (per > 1 && rows * (groups / per) < kCdfWaves) per /= 2;
+    while (per == 1 && parts < 32 && l.p.grid / (2 * parts) >= 8 && rows * groups * parts < kCdfWaves &&
+           (int64_t)l.S * parts * 2 <= 65535)
+      parts *= 2;
+    hipLaunchKernelGGL(w1_cdf, dim3((unsigned)((groups + 4 * per - 1) / (4 * per)), (l.R + 63) / 64, l.S * parts), dim3(256),
+                       0, st, wa, per, parts);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // register-resident slots per thread: R <= 1024 with 256 threads, else 1024 threads
+  // every pair up to kPairRanks; past them the counting sort, 1024 threads with register-resident slots
   const int R = l.R;
-  if (R <= 256) launch_score<256, 1>(wa, st);
-  else if (R <= 512) launch_score<256, 2>(wa, st);
-  else if (R <= 1024) launch_score<256, 4>(wa, st);
+  const dim3 blocks((unsigned)SK);
+  if (R <= 256) hipLaunchKernelGGL((w1_score_pairs<256, 1>), blocks, dim3(256), 0, st, wa);
+  else if (R <= 512) hipLaunchKernelGGL((w1_score_pairs<256, 2>), blocks, dim3(256), 0, st, wa);
+  else if (R <= kPairRanks) hipLaunchKernelGGL((w1_score_pairs<256, 4>), blocks, dim3(256), 0, st, wa);
   else if (R <= 2048) launch_score<1024, 2>(wa, st);
   else if (R <= 4096) launch_score<1024, 4>(wa, st);
   else if (R <= 8192) launch_score<1024, 8>(wa, st);

@@ -12,7 +12,7 @@ required to be rare).
 Cases: hand-built cluster sets (point masses, p99 below p50, non-positive
 percentiles, durations near 2^63, identical ranks, one present rank, too few
 ranks, malformed records, the smallest and a large grid, ragged rank counts
-up to the 16,384-rank limit), W1 over the oracle's own KDE clusters of the
+up to the 16,384-rank limit, rank counts and grids at the kernels' limits), W1 over the oracle's own KDE clusters of the
 tiny and medium traces, the full GPU chain summarize -> kde -> w1 on the tiny
 trace, and the production, cluster and skew workloads at full size in the
 launch configuration the benchmark times: there every KDE cell is compared
@@ -210,6 +210,24 @@ def test_w1_random_cluster_sets(R, S, K, seed):
     rng = np.random.default_rng(seed)
     ncl, cnt, a, b = _random_clusters(rng, R, S, K, malformed=3 if R >= 64 else 0)
     _both(ncl, cnt, a, b, R, S, K, f"random {R}x{S}x{K}")
+
+
+@pytest.mark.parametrize("R,G", [(2, 2), (3, 3), (8, 64), (31, 17), (63, 64), (64, 129), (65, 64), (255, 16), (256, 33),
+                                 (257, 40), (511, 8), (513, 64), (1023, 9), (1024, 64), (1025, 64)])
+def test_w1_rank_and_grid_edges(R, G):
+    """Rank counts around the limits of the pairwise score kernel (256 threads
+    of 1, 2 or 4 ranks, four-word rows; the sorting kernel past 1,024) and of
+    the CDF kernel's lane packing (64), grids that its workgroups split
+    unevenly, absent and malformed cells, kernel counts that leave wavefronts
+    part empty."""
+    _announce(f"w1 ranks {R} grid {G}")
+    rng = np.random.default_rng(R * 131 + G)
+    S, K = 2, 11
+    ncl, cnt, a, b = _random_clusters(rng, R, S, K, p_absent=0.2, outliers=0.1)
+    gw = pa.w1(_dev_clusters(ncl, cnt, a, b), R, S, K, grid=G, min_ranks=2)
+    torch.cuda.synchronize()
+    ow = oracle.w1(ncl, cnt, a, b, R, S, K, grid=G, min_ranks=2)
+    assert_w1_equal(gw, ow, R, S, K, f"ranks {R} grid {G}")
 
 
 def test_w1_malformed_records_are_reported():
