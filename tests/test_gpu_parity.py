@@ -336,6 +336,35 @@ def test_l1_golden_and_random():
             P.assert_float_close(g, o, ["cp_ratio"], f"l1 {R}x{S}")
 
 
+@pytest.mark.parametrize("S", [1, 2, 3, 5, 63, 64, 65, 128, 511, 513, 1023, 1024, 1025, 2047, 2049, 4095, 4096])
+def test_l1_series_length_edges(S):
+    """Series lengths around a wavefront's words and the LDS sizes; 32-bit
+    points and points up to 2^40 - 1, zero series, ties in the change point's
+    ratio, intervals across words and over the whole series, windows from one
+    point to more than the series."""
+    _announce(f"L1 series of {S} steps")
+    rng = np.random.default_rng(S)
+    R = 24
+    y = (10**6 * (1 + 0.05 * rng.standard_normal((R, S)))).astype(np.int64)
+    y[1::5, S // 2:] = y[1::5, S // 2:] * 3 // 2
+    y[2::5, S // 3] *= 3
+    y[3::5, S // 3:S // 3 + 70] *= 2
+    y[6::8] *= 1_000_000  # up to 2^40, past 32 bits
+    y = np.minimum(y, 2**40 - 1)
+    y[4] = 0
+    y[5] = 7
+    y[7] = np.where(np.arange(S) < S // 2, 1000, 1300)  # exactly rho
+    y[9] = rng.integers(1, 2**40, S)
+    y[11, :S // 4] = 0
+    for p in (dict(), dict(W=1), dict(W=70, min_seg=1, cmax_pm=150), dict(W=10_000, theta_pm=0, beta_pm=2**31 - 1),
+              dict(rho_pm=0, cmax_pm=1000, min_seg=3)):
+        g = pa.iter_windows(torch.from_numpy(y.reshape(-1)).to(DEV), R, S, **p)
+        torch.cuda.synchronize()
+        o = oracle.iter_windows(y.reshape(-1), R, S, **p)
+        P.assert_int_equal(g, o, P.L1_INT_FIELDS, f"l1 S={S} {p}")
+        P.assert_float_close(g, o, ["cp_ratio"], f"l1 S={S} {p}")
+
+
 @pytest.mark.parametrize("K,keyed", [(64, False), (2048, False), (6000, False), (40_000, False), (300, True)])
 def test_absent_cells_keep_their_buffers(K, keyed):
     """Only the count of an absent cell is written: its sum, min, max and
