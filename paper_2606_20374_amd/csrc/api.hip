@@ -366,8 +366,6 @@ int argus_compact(const argus_summary_t* sum, int32_t n_ranks, int32_t n_steps, 
   int rc = check_device();
   if (rc != ARGUS_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
-  rc = status_of(launch_clear(dev_status, nullptr, st));
-  if (rc != ARGUS_OK) return rc;
   CompactLaunch l{sum->count, sum->sum_ns, sum->min_ns, sum->max_ns, sum->hist, (int32_t)n_seg, n_cells, n_streams,
                   out, capacity, seg_byte_off, dev_status, static_cast<int64_t*>(workspace)};
   return status_of(launch_compact(l, st));

@@ -187,7 +187,7 @@ struct CompactLaunch {
   int64_t capacity;
   int64_t* seg_byte_off;
   int32_t* dev_status;
-  int64_t* sizes;  // workspace [n_seg]
+  int64_t* sizes;  // workspace [n_seg]: the segments' look-back states
 };
 hipError_t launch_compact(const CompactLaunch& a, hipStream_t st);
 

@@ -4,24 +4,40 @@
 // trace). The record layout is defined in include/argus.h.
 //
 // Launches, in order:
-//   compact_sizes   one workgroup per segment: the byte size of its records
-//                   (33 + 5 per nonzero octave bin for every present cell).
-//   compact_scan    one workgroup: exclusive prefix of the sizes in segment
-//                   order -> seg_byte_off (deterministic placement).
-//   compact_write   one workgroup per segment: 256 cells at a time, each
-//                   thread builds its cell's record in an LDS staging area at
-//                   the offset a block scan assigns, then the workgroup copies
-//                   the staged bytes to their final position with aligned
+//   compact_clear   the segments' states and the ticket counter.
+//   compact_kernel  one workgroup per segment (a wavefront per segment of up to
+//                   512 cells), in ticket order: each wavefront builds
+//                   the records of a contiguous range of cells in its own LDS
+//                   region, reading every summary field once; the
+//                   segment's size is published, the sizes of the segments
+//                   before it are added up (decoupled look-back), and the
+//                   regions are copied to their final place with aligned
 //                   4-byte stores (byte stores only at the two unaligned
-//                   ends). A record is written only if it lies entirely
-//                   inside the caller's buffer.
+//                   ends). Cells past a full region are only sized at first
+//                   and read again once the place is known. A record is
+//                   written only if it lies entirely inside the caller's
+//                   buffer.
+// 156 bytes of a present cell are read and 33 + 5 per nonzero bin written.
+// Cluster step (10,240 x 2,048 cells, 4.0 GB): 1,755 us when the histograms
+// were read once for sizes and once more for the records, a cell per thread;
+// 1,290 us now (3.1 TB/s), of which the loads alone take 632 us, building the
+// records 390 us (LDS: 5-byte entries at any alignment), the look-back 110 us
+// and the copies 155 us, timed by leaving each out.
 #include "argus_internal.h"
 
 namespace argus {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kRecMax = 33 + 5 * NB;  // largest record: every octave bin nonzero
+// Record bytes a wavefront stages: sixteen wavefronts share a CU's 160 KB.
+constexpr int kRegion = 9856;
+static_assert(8 * (33 + 5 * NB) <= kRegion, "a step of the largest records fits");
+constexpr int kGroup = 8;                 // lanes per cell: four octave bins each
+constexpr int64_t kMaxGrid = 1 << 20;     // workgroups per launch
+
+// Segment state, one word: 2 bits of state above 62 bits of bytes.
+constexpr uint64_t kSize = 1ull << 62;    // the segment's own bytes
+constexpr uint64_t kPrefix = 2ull << 62;  // the bytes of all segments up to this one
+constexpr uint64_t kBytes = kSize - 1;
 
 struct CompactArgs {
   const uint32_t* count;
@@ -32,163 +48,244 @@ struct CompactArgs {
   int32_t n_seg, n_cells, n_streams;
   uint8_t* out;
   int64_t cap;
-  int64_t* seg_off;
+  int64_t* seg_off;  // the last word is the ticket counter until the last segment writes the total there
   int32_t* dev_status;
-  int64_t* sizes;
+  uint64_t* state;
 };
 
-// nonzero-bin mask of one cell's octave histogram (16-byte loads)
-__device__ __forceinline__ uint32_t bin_mask(const uint32_t* h) {
-  uint32_t m = 0;
-  const uint4* h4 = reinterpret_cast<const uint4*>(h);
-#pragma unroll
-  for (int q = 0; q < NB / 4; ++q) {
-    const uint4 v = h4[q];
-    m |= (v.x != 0 ? 1u : 0u) << (4 * q);
-    m |= (v.y != 0 ? 1u : 0u) << (4 * q + 1);
-    m |= (v.z != 0 ? 1u : 0u) << (4 * q + 2);
-    m |= (v.w != 0 ? 1u : 0u) << (4 * q + 3);
+__global__ __launch_bounds__(256) void compact_clear(CompactArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < a.n_seg) a.state[i] = 0;
+  if (i == 0) {
+    a.seg_off[a.n_seg] = 0;
+    if (a.dev_status) *a.dev_status = 0;
   }
-  return m;
 }
 
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wtot, uint32_t& total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += t;
-  }
-  if (lane == 63) wtot[w] = inc;
-  __syncthreads();
-  uint32_t base = 0;
-  total = 0;
-#pragma unroll
-  for (int i = 0; i < kThreads / 64; ++i) {
-    const uint32_t x = wtot[i];
-    if (i < w) base += x;
-    total += x;
-  }
-  __syncthreads();
-  return base + inc - v;
+__device__ __forceinline__ void put4(uint8_t* p, uint32_t v) { __builtin_memcpy(p, &v, 4); }
+
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// ------------------------------------------------------------------- sizes
-__global__ __launch_bounds__(kThreads) void compact_sizes(CompactArgs a) {
-  __shared__ unsigned long long tot;
-  const int64_t g = blockIdx.x;
-  if (threadIdx.x == 0) tot = 0;
-  __syncthreads();
-  unsigned long long s = 0;
-  for (int c = threadIdx.x; c < a.n_cells; c += kThreads) {
-    const int64_t i = g * a.n_cells + c;
-    if (a.count[i] == 0) continue;
-    s += 33u + 5u * (uint32_t)__popc(bin_mask(a.hist + i * NB));
-  }
-  s = wave_sum_u64(s);
-  if ((threadIdx.x & 63) == 0) atomicAdd(&tot, s);
-  __syncthreads();
-  if (threadIdx.x == 0) a.sizes[g] = (int64_t)tot;
-}
+// Loaded steps of a wavefront: kGroup present cells each, kGroup lanes to a
+// cell; lane sub of a cell holds four octave bins and, where records are
+// built, one word of the record's head (sub 0: none).
+constexpr int kSet = 4;
+struct Steps {
+  int cell[kSet];  // cell index in the segment, or -1
+  uint4 h[kSet];
+  uint32_t field[kSet];
+};
 
-// -------------------------------------------------------------------- scan
-__global__ __launch_bounds__(1024) void compact_scan(CompactArgs a) {
-  __shared__ unsigned long long wtot[16];
-  __shared__ unsigned long long carry;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) carry = 0;
-  __syncthreads();
-  for (int64_t b = 0; b < a.n_seg; b += 1024) {
-    const int64_t g = b + tid;
-    const unsigned long long v = g < a.n_seg ? (unsigned long long)a.sizes[g] : 0ull;
-    unsigned long long inc = v;
+// A place in a wavefront's cells: a window of kWindow cells and a step among
+// its present cells.
+constexpr int kWindow = 256;
+struct Place {
+  int c, step;
+};
+
+// Sizes the present cells from p up to cell c1 of the segment whose cell 0 is
+// at row, adding to bytes. With kBuild their records are built in region while
+// they fit; p is left at the first step that does not. Returns the bytes
+// built. list: kWindow bytes of LDS of this wavefront. Two sets of steps
+// alternate, so that one set's loads are in flight while the other's records
+// are built.
+template <bool kBuild>
+__device__ __forceinline__ uint32_t take_cells(const CompactArgs& a, int64_t row, int c1, Place& p, uint8_t* region,
+                                               uint8_t* list, uint64_t& bytes) {
+  const int lane = threadIdx.x & 63, sub = lane & (kGroup - 1), grp = lane / kGroup;
+  const uint64_t below = (1ull << lane) - 1;
+  uint32_t at = 0;
+  for (; p.c < c1; p.c += kWindow, p.step = 0) {
+    const int c = p.c;
+    uint32_t cnt[kWindow / 64];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long t = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += t;
+    for (int q = 0; q < kWindow / 64; ++q) cnt[q] = c + 64 * q + lane < c1 ? a.count[row + c + 64 * q + lane] : 0u;
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < kWindow / 64; ++q) {
+      const uint64_t here = __ballot(cnt[q] != 0);
+      if (cnt[q] != 0) list[n + __popcll(here & below)] = (uint8_t)(64 * q + lane);
+      n += __popcll(here);
     }
-    if (lane == 63) wtot[w] = inc;
-    __syncthreads();
-    unsigned long long base = carry, total = 0;
-    for (int i = 0; i < 16; ++i) {
-      if (i < w) base += wtot[i];
-      total += wtot[i];
-    }
-    if (g < a.n_seg) a.seg_off[g] = (int64_t)(base + inc - v);
-    __syncthreads();
-    if (tid == 0) carry += total;
-    __syncthreads();
-  }
-  if (tid == 0) {
-    a.seg_off[a.n_seg] = (int64_t)carry;
-    if ((int64_t)carry > a.cap && a.dev_status) atomicOr(a.dev_status, (int32_t)ARGUS_DEV_COMPACT_CAPACITY);
-  }
-}
-
-// ------------------------------------------------------------------- write
-__device__ __forceinline__ void put(uint8_t* p, uint64_t v, int n) {
-  for (int i = 0; i < n; ++i) p[i] = (uint8_t)(v >> (8 * i));
-}
-
-__global__ __launch_bounds__(kThreads) void compact_write(CompactArgs a) {
-  __shared__ uint8_t stage[kThreads * kRecMax + 16];
-  __shared__ uint32_t wtot[kThreads / 64];
-  __shared__ uint32_t fit_end;
-  const int64_t g = blockIdx.x;
-  const int tid = threadIdx.x;
-  int64_t pos = a.seg_off[g];  // global byte position of the next chunk
-  if (pos >= a.cap) return;
-  for (int c0 = 0; c0 < a.n_cells; c0 += kThreads) {
-    const int c = c0 + tid;
-    const int64_t i = g * a.n_cells + c;
-    const bool present = c < a.n_cells && a.count[i] != 0;
-    const uint32_t m = present ? bin_mask(a.hist + i * NB) : 0u;
-    const uint32_t len = present ? 33u + 5u * (uint32_t)__popc(m) : 0u;
-    uint32_t chunk = 0;
-    const uint32_t at = block_excl_scan(len, wtot, chunk);
-    if (chunk == 0) continue;
-    if (tid == 0) fit_end = 0;
-    __syncthreads();
-    if (present) {
-      uint8_t* p = stage + at;
-      const uint32_t key = a.n_streams > 0 ? (uint32_t)(c / a.n_streams) | ((uint32_t)(c % a.n_streams) << 24)
-                                           : (uint32_t)c;
-      put(p, key, 4);
-      put(p + 4, a.count[i], 4);
-      put(p + 8, (uint64_t)a.sum[i], 8);
-      put(p + 16, (uint64_t)a.mn[i], 8);
-      put(p + 24, (uint64_t)a.mx[i], 8);
-      p[32] = (uint8_t)__popc(m);
-      int q = 33;
-      const uint32_t* h = a.hist + i * NB;
-      for (uint32_t mm = m; mm; mm &= mm - 1) {
-        const int b = __ffs(mm) - 1;
-        p[q] = (uint8_t)b;
-        put(p + q + 1, h[b], 4);
-        q += 5;
+    wave_order();
+    const int steps = (n + kGroup - 1) / kGroup;
+    auto load = [&](Steps& s, int first) {
+#pragma unroll
+      for (int u = 0; u < kSet; ++u) {
+        const int i = (first + u) * kGroup + grp;
+        s.cell[u] = i < n ? c + (int)list[i] : -1;
+        s.h[u] = make_uint4(0, 0, 0, 0);
+        s.field[u] = 0;
+        if (s.cell[u] < 0) continue;
+        const int64_t x = row + s.cell[u];
+        s.h[u] = reinterpret_cast<const uint4*>(a.hist + x * NB)[sub];
+        if (kBuild && sub != 0) {
+          const uint32_t* f = reinterpret_cast<const uint32_t*>((sub < 4 ? a.sum : (sub < 6 ? a.mn : a.mx)) + x) + (sub & 1);
+          s.field[u] = *(sub == 1 ? a.count + x : f);
+        }
       }
-      // records are written only when they lie entirely inside the buffer
-      if (pos + at + len <= a.cap) atomicMax(&fit_end, at + len);
-    }
-    __syncthreads();
-    // copy stage[0, fit_end) to out[pos, pos + fit_end)
-    const int64_t lo = pos, hi = pos + fit_end;
-    const int64_t wlo = (lo + 3) & ~(int64_t)3, whi = hi & ~(int64_t)3;
-    if (wlo < whi) {
-      for (int64_t wd = wlo + 4 * tid; wd < whi; wd += 4 * kThreads) {
-        const uint8_t* s = stage + (wd - lo);
-        const uint32_t v = (uint32_t)s[0] | ((uint32_t)s[1] << 8) | ((uint32_t)s[2] << 16) | ((uint32_t)s[3] << 24);
-        *reinterpret_cast<uint32_t*>(a.out + wd) = v;
+    };
+    // false: the region is full (p.step is the first step left)
+    auto take = [&](const Steps& s, int first) -> bool {
+#pragma unroll
+      for (int u = 0; u < kSet; ++u) {
+        if (first + u >= steps) break;
+        // places from the nonzero bins of the lanes below
+        const uint64_t b0 = __ballot(s.h[u].x != 0), b1 = __ballot(s.h[u].y != 0), b2 = __ballot(s.h[u].z != 0),
+                       b3 = __ballot(s.h[u].w != 0);
+        const int left = n - (first + u) * kGroup;
+        const uint32_t nz = (uint32_t)(__popcll(b0) + __popcll(b1) + __popcll(b2) + __popcll(b3));
+        const uint32_t len = 33u * (uint32_t)(left < kGroup ? left : kGroup) + 5u * nz;
+        if (kBuild) {
+          if (at + len > (uint32_t)kRegion) {
+            p.step = first + u;
+            return false;
+          }
+          uint32_t lower = 0;
+          for (const uint64_t b : {b0, b1, b2, b3})
+            lower = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, lower));
+          const uint32_t before = __shfl(lower, lane & ~(kGroup - 1), 64);  // those of the cells before this one
+          if (s.cell[u] >= 0) {
+            uint8_t* rec = region + at + 33u * (uint32_t)grp + 5u * before;
+            uint32_t v = s.field[u];
+            if (sub == 0)
+              v = a.n_streams > 0
+                      ? (uint32_t)(s.cell[u] / a.n_streams) | ((uint32_t)(s.cell[u] % a.n_streams) << 24)
+                      : (uint32_t)s.cell[u];
+            put4(rec + 4 * sub, v);
+            uint8_t* e = rec + 33 + 5u * (lower - before);
+            const uint32_t w[4] = {s.h[u].x, s.h[u].y, s.h[u].z, s.h[u].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              if (w[q] == 0) continue;
+              e[0] = (uint8_t)(4 * sub + q);
+              put4(e + 1, w[q]);
+              e += 5;
+            }
+            // the last lane of the cell knows its number of nonzero bins
+            if (sub == kGroup - 1) rec[32] = (uint8_t)((uint32_t)(e - rec - 33) / 5u);
+          }
+        }
+        at += len;
+        bytes += len;
       }
-      if (tid < wlo - lo) a.out[lo + tid] = stage[tid];
-      if (tid < hi - whi) a.out[whi + tid] = stage[whi - lo + tid];
-    } else {
-      for (int64_t b = lo + tid; b < hi; b += kThreads) a.out[b] = stage[b - lo];
+      return true;
+    };
+    Steps x, y;
+    load(x, p.step);
+    for (int s = p.step; s < steps; s += 2 * kSet) {
+      load(y, s + kSet);
+      if (!take(x, s)) return at;
+      load(x, s + 2 * kSet);
+      if (!take(y, s + kSet)) return at;
     }
-    pos += chunk;
-    __syncthreads();
-    if (pos >= a.cap) return;
+    wave_order();  // the list is used to here
+  }
+  return at;
+}
+
+// region[0, len) to out[pos, pos + len): the whole wavefront.
+__device__ __forceinline__ void copy_out(const CompactArgs& a, const uint8_t* region, uint32_t len, int64_t pos) {
+  const int lane = threadIdx.x & 63;
+  if (pos + (int64_t)len > a.cap) {
+    // the records up to the first that does not fit
+    uint32_t end = 0;
+    while (end < len) {
+      const uint32_t rec = 33u + 5u * region[end + 32];
+      if (pos + (int64_t)(end + rec) > a.cap) break;
+      end += rec;
+    }
+    len = end;
+  }
+  uint8_t* dst = a.out + pos;
+  const uint32_t skew = (uint32_t)((0 - reinterpret_cast<uintptr_t>(dst)) & 3u);
+  const uint32_t head = skew < len ? skew : len, words = (len - head) / 4, tail = (len - head) & 3u;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(region);
+  uint32_t* dw = reinterpret_cast<uint32_t*>(dst + head);
+  for (uint32_t i = lane; i < words; i += 64) dw[i] = __builtin_amdgcn_alignbyte(src[i + 1], src[i], head);
+  if ((uint32_t)lane < head) dst[lane] = region[lane];
+  if ((uint32_t)lane < tail) dst[head + 4 * words + lane] = region[head + 4 * words + lane];
+}
+
+// kOwn: every wavefront takes a segment of its own, else they share one.
+template <int kWaves, bool kOwn>
+__global__ __launch_bounds__(64 * kWaves, 4) void compact_kernel(CompactArgs a, int64_t n_wg) {
+  __shared__ alignas(16) uint8_t region_sh[kWaves][kRegion + 4];  // + a word that alignbyte may read past the end
+  __shared__ uint8_t list_sh[kWaves][kWindow];
+  __shared__ uint64_t wave_bytes[kWaves];
+  __shared__ int64_t seg_sh, pos_sh;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // tickets number the segments in the order their workgroups started, so
+  // every segment waited for below belongs to a workgroup that is running and
+  // publishes its size without waiting for any other
+  if (tid == 0) seg_sh = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(a.seg_off + a.n_seg), 1ull);
+  lds_barrier();
+  const int64_t b = seg_sh;  // this workgroup's place: segments kWaves b on, or segment b
+  uint8_t* region = region_sh[w];
+  const int64_t g = kOwn ? b * kWaves + w : b;
+  const int64_t row = g * a.n_cells;
+  const int per = kOwn ? a.n_cells : ((a.n_cells + kWaves - 1) / kWaves + 63) / 64 * 64;
+  const int c0 = kOwn ? (g < a.n_seg ? 0 : a.n_cells) : (int)((int64_t)per * w < a.n_cells ? (int64_t)per * w : a.n_cells);
+  const int c1 = (int)((int64_t)c0 + per < a.n_cells ? (int64_t)c0 + per : a.n_cells);
+  uint64_t bytes = 0;
+  uint32_t staged = 0;
+  Place p{c0, 0};
+  int64_t pos = 0;
+  for (bool placed = false;;) {
+    if (a.cap > 0) staged = take_cells<true>(a, row, c1, p, region, list_sh[w], bytes);
+    if (!placed) {
+      placed = true;
+      Place rest = p;
+      take_cells<false>(a, row, c1, rest, region, list_sh[w], bytes);
+      if (lane == 0) wave_bytes[w] = bytes;
+      lds_barrier();
+      uint64_t before = 0, all = 0;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        before += v < w ? wave_bytes[v] : 0;
+        all += wave_bytes[v];
+      }
+      if (w == 0) {
+        uint64_t excl = 0;
+        if (b > 0) {
+          if (lane == 0) __hip_atomic_store(&a.state[b], kSize | all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          // 64 predecessors at a time, nearest first, up to one whose prefix is known
+          for (int64_t base = b - 1;;) {
+            const int64_t i = base - lane;
+            const uint64_t st = i >= 0 ? __hip_atomic_load(&a.state[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kPrefix;
+            const uint64_t known = __ballot(st >> 62 == 2), none = __ballot(st >> 62 == 0);
+            const int first = known ? __builtin_ctzll(known) : 63;
+            if (none & (~0ull >> (63 - first))) {
+              __builtin_amdgcn_s_sleep(1);
+              continue;
+            }
+            excl += wave_sum_u64(lane <= first ? st & kBytes : 0ull);
+            if (known) break;
+            base -= 64;
+          }
+        }
+        if (lane == 0) {
+          __hip_atomic_store(&a.state[b], kPrefix | (excl + all), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          pos_sh = (int64_t)excl;
+          if (b == n_wg - 1) {  // every ticket has been taken
+            a.seg_off[a.n_seg] = (int64_t)(excl + all);
+            if ((int64_t)(excl + all) > a.cap && a.dev_status) atomicOr(a.dev_status, (int32_t)ARGUS_DEV_COMPACT_CAPACITY);
+          }
+        }
+      }
+      lds_barrier();
+      pos = pos_sh + (int64_t)before;
+      if (lane == 0 && g < a.n_seg && (kOwn || w == 0)) a.seg_off[g] = pos;
+    }
+    if (staged == 0 || pos >= a.cap) break;
+    copy_out(a, region, staged, pos);
+    pos += staged;
+    if (p.c >= c1) break;
+    wave_order();
   }
 }
 
@@ -196,17 +293,23 @@ __global__ __launch_bounds__(kThreads) void compact_write(CompactArgs a) {
 
 hipError_t launch_compact(const CompactLaunch& l, hipStream_t st) {
   CompactArgs a{l.count, l.sum_ns, l.min_ns, l.max_ns, l.hist, l.n_seg, l.n_cells, l.n_streams, l.out, l.capacity,
-                l.seg_byte_off, l.dev_status, l.sizes};
-  if (l.n_seg > 0) {
-    hipLaunchKernelGGL(compact_sizes, dim3(l.n_seg), dim3(kThreads), 0, st, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(compact_scan, dim3(1), dim3(1024), 0, st, a);
+                l.seg_byte_off, l.dev_status, reinterpret_cast<uint64_t*>(l.sizes)};
+  hipLaunchKernelGGL(compact_clear, dim3((unsigned)(((int64_t)l.n_seg + 255) / 256 + (l.n_seg == 0 ? 1 : 0))), dim3(256), 0,
+                     st, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || l.n_seg == 0 || l.capacity == 0) return e;
-  hipLaunchKernelGGL(compact_write, dim3(l.n_seg), dim3(kThreads), 0, st, a);
-  return hipGetLastError();
+  // A segment of more than 512 cells takes a workgroup of four or eight
+  // wavefronts; smaller ones a wavefront each, which also keeps the chain of
+  // places short (10,000 segments of 60 cells: 174 us with a workgroup each).
+  const bool own = l.n_cells <= 512;
+  const int64_t n_wg = own ? ((int64_t)l.n_seg + 7) / 8 : l.n_seg;
+  for (int64_t s = 0; s < n_wg && e == hipSuccess; s += kMaxGrid) {
+    const dim3 n((unsigned)(n_wg - s < kMaxGrid ? n_wg - s : kMaxGrid));
+    if (own) hipLaunchKernelGGL((compact_kernel<8, true>), n, dim3(512), 0, st, a, n_wg);
+    else if (l.n_cells <= 1024) hipLaunchKernelGGL((compact_kernel<4, false>), n, dim3(256), 0, st, a, n_wg);
+    else hipLaunchKernelGGL((compact_kernel<8, false>), n, dim3(512), 0, st, a, n_wg);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 }  // namespace argus

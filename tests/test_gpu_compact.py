@@ -5,7 +5,8 @@ record stream must match exactly, with identical segment offsets.
 Cases: random events whose kernels run on several streams (with invalid
 records), key spaces in the dense and the mapped (two passes) layout, the
 tiny trace with re-drawn streams, the record stream of both keyings,
-truncation at a short capacity and sizing at capacity 0, and full-size
+truncation at a short capacity and sizing at capacity 0, cell counts and
+record sizes at the kernel's limits, and full-size
 production and cluster summaries compacted in the launch configuration the
 benchmark times.
 """
@@ -120,6 +121,42 @@ def test_compact_kernel_keys_capacity_and_sizing():
     torch.cuda.synchronize()
     assert rc == 0 and int(off[-1].item()) == total
     assert int(st.item()) == (pa.argus.DEV_COMPACT_CAPACITY if total > 0 else 0)
+
+
+@pytest.mark.parametrize("G,C,fill", [(1, 1, 0.9), (9, 63, 0.5), (70, 64, 1.0), (300, 65, 0.02), (17, 256, 0.7),
+                                      (5, 511, 1.0), (8, 512, 0.3), (9, 513, 0.9), (3, 1024, 1.0), (70, 1025, 0.05),
+                                      (4, 2048, 1.0), (3, 5000, 0.6), (130, 3, 0.0)])
+@pytest.mark.parametrize("bins", [2, 32])
+def test_compact_cell_counts_and_full_records(G, C, fill, bins):
+    """Cell counts around a wavefront's window and the sizes at which segments
+    change from a wavefront to a workgroup each, segment counts past one
+    look-back window, empty segments, records of every octave bin (more bytes
+    than a wavefront stages, so the rest is read again), every alignment of
+    the caller's buffer, and capacities that cut inside a record."""
+    _announce(f"compact G={G} C={C} fill={fill} bins={bins}")
+    rng = np.random.default_rng(G * 10_007 + C * 31 + bins)
+    n = G * C
+    cnt = np.where(rng.random(n) < fill, rng.integers(1, 2**32, n), 0).astype(np.uint32)
+    cnt[rng.integers(0, n)] = 0
+    hist = rng.integers(1, 2**32, size=(n, 32)).astype(np.uint32)
+    hist[rng.random((n, 32)) >= (1.0 if bins == 32 else bins / 32)] = 0
+    f = lambda: rng.integers(-2**62, 2**62, n)  # noqa: E731
+    o = {"count": cnt, "sum_ns": f(), "min_ns": f(), "max_ns": f(), "hist": hist.reshape(-1)}
+    s = {k: torch.from_numpy(v.view(np.int32) if v.dtype == np.uint32 else v).to(DEV) for k, v in o.items()}
+    _compact_both(s, o, G, C, 0, "sized")
+    ob, ooff = oracle.compact(o, G, C, 0)
+    total = int(ooff[-1])
+    for skew, cap in ((1, total), (2, total + 3), (3, max(total - 1, 0)), (7, total // 2), (0, min(total, 20))):
+        buf = torch.full((total + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+        g = pa.compact(s, G, 1, C, 0, capacity=cap, out=buf[skew:])
+        torch.cuda.synchronize()
+        assert np.array_equal(g["seg_byte_off"].cpu().numpy(), ooff)
+        want, end = np.full(total + 64, 0xA5, np.uint8), 0
+        while end < total and end + 33 + 5 * int(ob[end + 32]) <= cap:
+            end += 33 + 5 * int(ob[end + 32])
+        want[skew:skew + end] = ob[:end]
+        assert np.array_equal(buf.cpu().numpy(), want), (skew, cap)
+        assert int(g["dev_status"].item()) == (pa.argus.DEV_COMPACT_CAPACITY if cap < total else 0)
 
 
 @pytest.mark.parametrize("name", ["production", "cluster"])
