@@ -234,19 +234,24 @@ __device__ __forceinline__ uint32_t quant16(double v) {
 
 // The lanes are ranks; fewer than 64 ranks leave room for those of
 // several kernel ids, of which a wavefront takes k_per_wave (lane groups
-// together) in turn. g_parts workgroups share the grid points.
-__global__ __launch_bounds__(256) void w1_cdf(W1Args a, int k_per_wave, int g_parts) {
+// together) in turn. g_parts workgroups share the grid points. SPLIT false:
+// at least 64 ranks, kCdfKPerWave ids and one part, as constants (10,240
+// ranks x 2,048 kernels: 3.70 ms with them as arguments, 3.56 with these).
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void w1_cdf(W1Args a, int k_per_wave_, int g_parts_) {
+  const int k_per_wave = SPLIT ? k_per_wave_ : kCdfKPerWave, g_parts = SPLIT ? g_parts_ : 1;
   __shared__ double tab[kPhiN * 4];
   for (int i = threadIdx.x; i < kPhiN * 4; i += 256) tab[i] = g_phi_tab[i];
   __syncthreads();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int pack = a.R < 64 ? 64 / a.R : 1;
-  const int r = a.R < 64 ? lane % a.R : blockIdx.y * 64 + lane;
+  const bool few = SPLIT && a.R < 64;
+  const int pack = few ? 64 / a.R : 1;
+  const int r = few ? lane % a.R : blockIdx.y * 64 + lane;
   const int s = blockIdx.z / g_parts, part = blockIdx.z % g_parts;
   const int g_from = (int)((int64_t)a.G * part / g_parts), g_to = (int)((int64_t)a.G * (part + 1) / g_parts);
-  if (r >= a.R || (a.R < 64 && lane >= pack * a.R)) return;
+  if (r >= a.R || (few && lane >= pack * a.R)) return;
   for (int j = 0; j < k_per_wave; ++j) {
-    const int k = ((blockIdx.x * 4 + w) * k_per_wave + j) * pack + (a.R < 64 ? lane / a.R : 0);
+    const int k = ((blockIdx.x * 4 + w) * k_per_wave + j) * pack + (few ? lane / a.R : 0);
     if (k >= a.K) break;
     const int64_t sk = (int64_t)s * a.K + k;
     if (!evaluated(a, a.o.n_present[sk])) continue;
@@ -961,8 +966,11 @@ hipError_t launch_w1(const W1Launch& l, hipStream_t st) {
     while (per == 1 && parts < 32 && l.p.grid / (2 * parts) >= 8 && rows * groups * parts < kCdfWaves &&
            (int64_t)l.S * parts * 2 <= 65535)
       parts *= 2;
-    hipLaunchKernelGGL(w1_cdf, dim3((unsigned)((groups + 4 * per - 1) / (4 * per)), (l.R + 63) / 64, l.S * parts), dim3(256),
-                       0, st, wa, per, parts);
+    const dim3 grid((unsigned)((groups + 4 * per - 1) / (4 * per)), (l.R + 63) / 64, l.S * parts);
+    if (l.R >= 64 && per == kCdfKPerWave)
+      hipLaunchKernelGGL(w1_cdf<false>, grid, dim3(256), 0, st, wa, per, parts);
+    else
+      hipLaunchKernelGGL(w1_cdf<true>, grid, dim3(256), 0, st, wa, per, parts);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
