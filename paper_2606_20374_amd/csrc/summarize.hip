@@ -12,16 +12,19 @@
 //   loads of four consecutive events per thread, software pipelined so the
 //   next group is in flight while the current one is processed.
 // * Per-kernel state is privatised in LDS: 64-bit sum, min and max, and a
-//   WIN-bin window of the octave histogram anchored at the first duration
-//   seen for that kernel (a lognormal mode spans two or three octaves; ten
-//   bins also hold kernels whose positions run at 1x, 3x and 9x). Bins
-//   outside the window go to a small pool of full 32-bin records that a
-//   kernel claims on first need.
+//   WIN-bin window of the octave histogram (a lognormal mode spans two or
+//   three octaves, a kernel whose positions run at 1x, 3x and 9x five or
+//   six). In the dense layout the window has ten bins around the first
+//   duration seen; where the map or table leaves room for six only, bin b is
+//   counted at b mod 6 while the bins seen span at most six octaves, wherever
+//   the first lay. Bins outside the window go to a small pool of full 32-bin
+//   records that a kernel claims on first need.
 // * Keys (kernel ids, or (kernel id, stream) pairs as id * n_streams +
 //   stream: section 5.2 groups per kernel and stream) map to LDS slots
-//   directly when the key space fits (dense), or through an LDS key->slot
-//   map that hands out slots on first sight (mapped), so a large, sparse key
-//   space takes one pass per 16,384 keys.
+//   directly when the key space fits (dense), through an LDS key->slot map
+//   that hands out slots on first sight (mapped, up to 16,384 keys), or
+//   through an LDS hash table of the keys seen (hashed, up to 65,536 keys),
+//   so a large, sparse key space too is read once.
 // * Whenever the pool or the slots run out, the kernels concerned are
 //   marked and redone exactly in another pass over the segment: the result
 //   is exact for every input; typical traces need one pass.
@@ -43,10 +46,11 @@ typedef long long v2l __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 1024;
 constexpr int kPool = 32;  // full 32-bin records per pass
-constexpr uint32_t kBaseUnset = 0xFFu;
+constexpr uint32_t kSpanMask = 0x3E00FFu;
+constexpr uint32_t kSpanUnset = 0xFFu;  // first bin of a span: none seen yet
 constexpr uint32_t kStNone = 0, kStBusy = 0xFE, kStPoison = 0xFF;
 constexpr uint32_t kDone = 1u << 16;
-constexpr int kMapIds = 16384;  // ids per pass in mapped mode
+constexpr int kMapIds = 16384;  // ids in mapped mode
 // Bound on the iterations of one claim wait, and on the passes over one key
 // range that may end with a wait cut short. A claim's owner publishes after
 // a fixed number of its own instructions, so no wait comes near the bound
@@ -54,16 +58,29 @@ constexpr int kMapIds = 16384;  // ids per pass in mapped mode
 // exit (and report) in that case instead of hanging.
 constexpr int kSpinCap = 1 << 16;
 constexpr int kMaxStuckPasses = 4;
+// Hashed mode: 2,048 buckets of four entries (one 16-byte LDS read), at most
+// a quarter full, so all but about 0.5% of the keys lie in their own bucket.
+constexpr int kHashIds = ARGUS_MAX_KERNELS;  // every key space is one range in hashed mode
+constexpr int kHash = 8192, kBucketShift = 32 - 11;
+constexpr uint32_t kHashEmpty = 0xFFFFFFFFu, kTagBits = 12, kTagMask = 0xFFF, kTagBusy = 0xFFE, kTagDefer = 0xFFD;
+constexpr int kDense = 0, kMapped = 1, kHashed = 2;
 constexpr uint32_t kMapEmpty = 0xFFFF, kMapBusy = 0xFFFE, kMapDefer = 0xFFFD, kMapDone = 0xFFFC;
 
-// meta word of a slot: bits 0-7 window base bin (0xFF unset), bits 8-15
-// full-record state (0 none, 1..kPool record index + 1, 0xFE being claimed,
-// 0xFF pool exhausted: redo in another pass), bit 16 already written.
+// meta word of a slot: bits 0-7 first bin of the window's span (0xFF unset),
+// bits 17-21 its last bin (not kept in dense mode: first + WIN - 1), bits 8-15 full-record state (0 none, 1..kPool
+// record index + 1, 0xFE being claimed, 0xFF pool exhausted: redo in another
+// pass), bit 16 already written.
 //
 // map entry (mapped mode, 16 bits, two per 32-bit word): a slot index, or
 // empty / being claimed / deferred to another pass / already written.
+//
+// hash entry (hashed mode, 32 bits): local id << 12 | slot index, or being
+// claimed / deferred in the slot's place; empty is all ones. The table is
+// filled afresh in every pass; ids already written have their bit in done.
 
-template <int NSLOT, int WIN, bool MAPPED>
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+template <int NSLOT, int WIN, int MODE>
 struct Smem {
   unsigned long long sum[NSLOT];
   long long mm[NSLOT][2];  // min, max (one 16-byte read per event)
@@ -71,8 +88,9 @@ struct Smem {
   uint32_t meta[NSLOT];
   uint32_t pool[kPool][NB];
   unsigned long long stream_busy[ARGUS_MAX_STREAMS];
-  uint32_t map[MAPPED ? kMapIds / 2 : 1];
-  uint16_t slot_kid[MAPPED ? NSLOT : 1];
+  alignas(16) uint32_t map[MODE == kMapped ? kMapIds / 2 : MODE == kHashed ? kHash : 1];
+  uint32_t done[MODE == kHashed ? kHashIds / 32 : 1];
+  uint16_t slot_kid[MODE != kDense ? NSLOT : 1];
   unsigned long long red_busy, red_wire;
   long long red_first, red_last;
   uint32_t red_valid, red_invalid;
@@ -108,9 +126,9 @@ struct Args {
   int32_t* dev_status;
 };
 
-template <int NSLOT, int WIN, bool MAPPED>
+template <int NSLOT, int WIN, int MODE>
 struct Seg {
-  using S = Smem<NSLOT, WIN, MAPPED>;
+  using S = Smem<NSLOT, WIN, MODE>;
   S& sm;
 
   __device__ __forceinline__ uint16_t map_get(int lk) const {
@@ -170,6 +188,80 @@ struct Seg {
     return res;
   }
 
+  __device__ __forceinline__ static int hash_bucket(int lk) {
+    return (int)(((uint32_t)lk * 0x9E3779B1u) >> kBucketShift);
+  }
+
+  // The slot of lk if its own bucket e holds it; else -2.
+  __device__ __forceinline__ static int hash_find(int lk, const v4u& e) {
+    int r = -2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t s = e[i] ^ ((uint32_t)lk << kTagBits);  // below NSLOT only for lk's published entry
+      r = s < (uint32_t)NSLOT ? (int)s : r;
+    }
+    return r;
+  }
+
+  // Slot of local id lk, which its bucket (read as e) does not hold with a
+  // slot: claims the first empty entry from the bucket on, or finds the id
+  // further on; -1 when the id is already written or has no slot in this
+  // pass. Entries only go from empty to claimed to published, so the stale
+  // read e can only start the walk early. At most NSLOT ids and one more per
+  // thread are inserted, so the walk always meets an empty entry. Same exit
+  // discipline as map_claim.
+  __device__ int hash_claim(int lk, const v4u& e0) {
+    int res = (sm.done[lk >> 5] >> (lk & 31)) & 1u ? -1 : -2;
+    const uint32_t mine = (uint32_t)lk << kTagBits;
+    int skip = 4;
+#pragma unroll
+    for (int i = 3; i >= 0; --i) skip = e0[i] == kHashEmpty || (e0[i] & ~kTagMask) == mine ? i : skip;
+    int pos = (hash_bucket(lk) * 4 + skip) & (kHash - 1);
+    for (int it = 0;; ++it) {
+      if (res == -2 && it >= kSpinCap) {
+        lds_store(&sm.stuck, 1u);
+        res = -1;
+      }
+      if (res == -2) {
+        uint32_t e = lds_load(&sm.map[pos]);
+        if (e == kHashEmpty) {
+          if (lds_load(&sm.nslots) >= (uint32_t)NSLOT) {
+            lds_store(&sm.poison, 1u);
+            res = -1;
+          } else {
+            e = atomicCAS(&sm.map[pos], kHashEmpty, mine | kTagBusy);
+            if (e == kHashEmpty) {
+              const uint32_t s = atomicAdd(&sm.nslots, 1u);
+              uint32_t tag = kTagDefer;
+              if (s < (uint32_t)NSLOT) {
+                sm.slot_kid[s] = (uint16_t)lk;
+                tag = s;
+                res = (int)s;
+              } else {
+                lds_store(&sm.poison, 1u);
+                res = -1;
+              }
+              lds_store(&sm.map[pos], mine | tag);
+            }
+          }
+        }
+        if (res == -2 && e != kHashEmpty) {
+          if ((e & ~kTagMask) != mine) {
+            pos = (pos + 1) & (kHash - 1);
+          } else {
+            const uint32_t tag = e & kTagMask;
+            if (tag < (uint32_t)NSLOT)
+              res = (int)tag;
+            else if (tag == kTagDefer)
+              res = -1;
+          }
+        }
+      }
+      if (!__any(res == -2)) break;
+    }
+    return res;
+  }
+
   // Count bin b outside the inline window in a full pool record, claiming
   // one for the slot on first need (same exit discipline as map_claim).
   __device__ void pool_add(int slot, uint32_t m, int b) {
@@ -216,19 +308,57 @@ struct Seg {
   // mmv: min and max of the slot as read before this event (possibly stale:
   // min only falls and max only rises, so a stale read can only cause an
   // extra atomic, never a missed one)
+  // Span of the window in meta word m (its first bin set), first and last
+  // bin, and the place of bin b of the span in the window.
+  __device__ __forceinline__ static int span_lo(uint32_t m) { return (int)(m & 0xFFu); }
+  __device__ __forceinline__ static int span_hi(uint32_t m) {
+    return MODE == kDense ? span_lo(m) + WIN - 1 : (int)((m >> 17) & 31u);
+  }
+  __device__ __forceinline__ static int win_at(uint32_t m, int b) {
+    static_assert(MODE == kDense || WIN == 6, "b * 43 >> 8 is b / 6 up to 31");
+    return MODE == kDense ? b - span_lo(m) : b - WIN * ((b * 43) >> 8);
+  }
+
+  // Mapped and hashed modes: widen the span of slot's window to hold bin b (m: its meta word, updated
+  // to the newest read); false when that would pass WIN octaves. Spans only
+  // widen and a state changes at most twice, and a failed swap means that
+  // another lane's succeeded, so the loop ends after a bounded count.
+  __device__ bool span_widen(int slot, uint32_t& m, int b) {
+    while (true) {
+      const bool unset = (m & 0xFFu) == kSpanUnset;
+      const int lo = unset || b < span_lo(m) ? b : span_lo(m);
+      const int hi = unset || b > span_hi(m) ? b : span_hi(m);
+      if (hi - lo >= WIN) return false;
+      const uint32_t want = (m & ~kSpanMask) | (uint32_t)lo | ((uint32_t)hi << 17);
+      if (want == m) return true;
+      const uint32_t old = atomicCAS(&sm.meta[slot], m, want);
+      if (old == m) {
+        m = want;
+        return true;
+      }
+      m = old;
+    }
+  }
+
   __device__ __forceinline__ void slot_add(int slot, uint32_t m, uint64_t d, const v2l& mmv) {
     if (m & kDone) return;
     const int b = octave_bin(d);
-    if ((m & 0xFFu) == kBaseUnset) {
-      int base = b - WIN / 2 + 1;
-      base = base < 0 ? 0 : (base > NB - WIN ? NB - WIN : base);
-      const uint32_t want = (m & ~0xFFu) | (uint32_t)base;
-      const uint32_t old = atomicCAS(&sm.meta[slot], m, want);
-      m = (old == m) ? want : old;
+    bool in;
+    if (MODE == kDense) {
+      if ((m & 0xFFu) == kSpanUnset) {
+        int base = b - WIN / 2 + 1;
+        base = base < 0 ? 0 : (base > NB - WIN ? NB - WIN : base);
+        const uint32_t want = (m & ~0xFFu) | (uint32_t)base;
+        const uint32_t old = atomicCAS(&sm.meta[slot], m, want);
+        m = (old == m) ? want : old;
+      }
+      in = (unsigned)(b - span_lo(m)) < (unsigned)WIN;
+    } else {
+      // unset: the first bin reads as 255, so no bin lies in the span
+      in = (b >= span_lo(m) && b <= span_hi(m)) || span_widen(slot, m, b);
     }
-    const int off = b - (int)(m & 0xFFu);
-    if ((unsigned)off < (unsigned)WIN)
-      atomicAdd(&sm.win[slot][off], 1u);
+    if (in)
+      atomicAdd(&sm.win[slot][win_at(m, b)], 1u);
     else
       pool_add(slot, m, b);
     atomicAdd(&sm.sum[slot], (unsigned long long)d);
@@ -242,14 +372,14 @@ struct Seg {
     sm.mm[s][1] = INT64_MIN;
 #pragma unroll
     for (int w = 0; w < WIN; ++w) sm.win[s][w] = 0;
-    sm.meta[s] = kBaseUnset;
+    sm.meta[s] = kSpanUnset;
   }
 };
 
 // Four events of one thread: validity and per-segment aggregates, then the
 // per-kernel updates.
-template <int NSLOT, int WIN, bool MAPPED>
-__device__ __forceinline__ void process4(Seg<NSLOT, WIN, MAPPED>& sg, const Args& a, const int32_t (&kid)[4],
+template <int NSLOT, int WIN, int MODE>
+__device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& a, const int32_t (&kid)[4],
                                          const int32_t (&st)[4], const int64_t (&t0)[4], const int64_t (&t1)[4],
                                          int n, bool first_scan, int kb, int nk, uint32_t& nv, uint32_t& ni,
                                          unsigned long long& busy, long long& tf, long long& tl) {
@@ -280,7 +410,17 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MAPPED>& sg, const Args
 #pragma unroll
   for (int h = 0; h < 4; h += 2) {
     int slot[2];
-    if (MAPPED) {
+    if (MODE == kHashed) {
+      v4u e[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        e[j] = *reinterpret_cast<const v4u*>(&sg.sm.map[sg.hash_bucket(lk[h + j] >= 0 ? lk[h + j] : 0) * 4]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        slot[j] = lk[h + j] >= 0 ? sg.hash_find(lk[h + j], e[j]) : -1;
+        if (slot[j] == -2) slot[j] = sg.hash_claim(lk[h + j], e[j]);
+      }
+    } else if (MODE == kMapped) {
       uint32_t e[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) e[j] = lk[h + j] >= 0 ? sg.map_get(lk[h + j]) : kMapDone;
@@ -307,11 +447,11 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MAPPED>& sg, const Args
   }
 }
 
-template <int NSLOT, int WIN, bool MAPPED>
+template <int NSLOT, int WIN, int MODE>
 __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
-  __shared__ Smem<NSLOT, WIN, MAPPED> sm;
+  __shared__ Smem<NSLOT, WIN, MODE> sm;
   __shared__ int64_t g_next;
-  Seg<NSLOT, WIN, MAPPED> sg{sm};
+  Seg<NSLOT, WIN, MODE> sg{sm};
   const int tid = threadIdx.x;
   const int32_t K = a.n_keys, NS = a.n_streams;
 
@@ -361,17 +501,21 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
   long long tf = INT64_MAX, tl = INT64_MIN;
   bool first_scan = true;
   int n_stuck = 0;  // passes of this segment that ended with a wait cut short
-  constexpr int kRange = MAPPED ? kMapIds : NSLOT;
+  constexpr int kRange = MODE == kHashed ? kHashIds : MODE == kMapped ? kMapIds : NSLOT;
 
   for (int32_t kb = 0; kb < K; kb += kRange) {
     const int nk = K - kb < kRange ? K - kb : kRange;
-    if (MAPPED)
+    if (MODE == kHashed)
+      for (int i = tid; i < kHashIds / 32; i += kThreads) sm.done[i] = 0;
+    else if (MODE == kMapped)
       for (int i = tid; i < kMapIds / 2; i += kThreads) sm.map[i] = 0xFFFFFFFFu;
     else
       for (int s = tid; s < nk; s += kThreads) sg.slot_reset(s);
     while (true) {
-      // mapped mode hands out slots afresh in every pass
-      if (MAPPED)
+      // the mapped and hashed modes hand out slots afresh in every pass
+      if (MODE == kHashed)
+        for (int i = tid; i < kHash; i += kThreads) sm.map[i] = kHashEmpty;
+      if (MODE != kDense)
         for (int s = tid; s < NSLOT; s += kThreads) sg.slot_reset(s);
       for (int i = tid; i < kPool * NB; i += kThreads) (&sm.pool[0][0])[i] = 0;
       if (tid == 0) {
@@ -470,7 +614,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
 
       // flush: the count of every slot; sum, min, max and wire size of the
       // present ones
-      const int nslot = MAPPED ? (int)(sm.nslots < (uint32_t)NSLOT ? sm.nslots : NSLOT) : nk;
+      const int nslot = MODE != kDense ? (int)(sm.nslots < (uint32_t)NSLOT ? sm.nslots : NSLOT) : nk;
       for (int s = tid; s < (redo_pass ? 0 : nslot); s += kThreads) {
         const uint32_t m = sm.meta[s];
         const uint32_t pst = (m >> 8) & 0xFFu;
@@ -487,7 +631,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
             nnz += sm.pool[pst - 1][b] != 0;
           }
         }
-        const int64_t c = g * K + kb + (MAPPED ? (int)sm.slot_kid[s] : s);
+        const int64_t c = g * K + kb + (MODE != kDense ? (int)sm.slot_kid[s] : s);
         a.count[c] = cnt;
         if (cnt) {
           a.sum_ns[c] = (int64_t)sm.sum[s];
@@ -496,23 +640,21 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
           wire += 33u + 5u * nnz;
         }
       }
-      // flush: histograms of the present slots (their window base is set),
+      // flush: histograms of the present slots (their span is set),
       // four bins per thread, 16-byte stores
       for (int it = tid; it < (redo_pass ? 0 : nslot) * (NB / 4); it += kThreads) {
         const int s = it >> 3, q = it & 7;
         const uint32_t m = sm.meta[s];
         const uint32_t pst = (m >> 8) & 0xFFu;
-        const int base = (int)(m & 0xFFu);
-        if ((m & kDone) || pst == kStPoison || base == (int)kBaseUnset) continue;
+        if ((m & kDone) || pst == kStPoison || (m & 0xFFu) == kSpanUnset) continue;
         uint32_t v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int b = 4 * q + j;
-          const int off = b - base;
-          v[j] = (unsigned)off < (unsigned)WIN ? sm.win[s][off] : 0u;
+          v[j] = b >= sg.span_lo(m) && b <= sg.span_hi(m) ? sm.win[s][sg.win_at(m, b)] : 0u;
           if (pst != kStNone) v[j] += sm.pool[pst - 1][b];
         }
-        const int64_t c = g * K + kb + (MAPPED ? (int)sm.slot_kid[s] : s);
+        const int64_t c = g * K + kb + (MODE != kDense ? (int)sm.slot_kid[s] : s);
         *reinterpret_cast<uint4*>(a.hist + c * NB + 4 * q) = make_uint4(v[0], v[1], v[2], v[3]);
       }
       lds_barrier();
@@ -522,7 +664,10 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
         const uint32_t m = sm.meta[s];
         if (m & kDone) continue;
         const bool redo = redo_pass || ((m >> 8) & 0xFFu) == kStPoison;
-        if (MAPPED) {
+        if (MODE == kHashed) {
+          const uint32_t k = sm.slot_kid[s];
+          if (!redo) atomicOr(&sm.done[k >> 5], 1u << (k & 31));
+        } else if (MODE == kMapped) {
           sg.map_set(sm.slot_kid[s], redo ? (uint16_t)kMapEmpty : (uint16_t)kMapDone);
         } else if (redo) {
           sg.slot_reset(s);
@@ -530,17 +675,18 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
           sm.meta[s] = m | kDone;
         }
       }
-      if (MAPPED)
+      if (MODE == kMapped)
         for (int i = tid; i < nk; i += kThreads)
           if (sg.map_get(i) == kMapDefer) sg.map_set(i, (uint16_t)kMapEmpty);
       lds_barrier();
       if (!again) break;
     }
-    if (MAPPED) {
+    if (MODE != kDense) {
       // keys of this range that never occurred: count 0 (their other fields
       // are not written)
       for (int i = tid; i < nk; i += kThreads)
-        if (sg.map_get(i) == kMapEmpty) a.count[g * K + kb + i] = 0;
+        if (MODE == kHashed ? !((sm.done[i >> 5] >> (i & 31)) & 1u) : sg.map_get(i) == kMapEmpty)
+          a.count[g * K + kb + i] = 0;
       lds_barrier();
     }
   }
@@ -574,7 +720,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
 
 // Workgroups resident at once (one per CU for the large tables): the grid
 // of the persistent kernel. Cached per device and instantiation.
-template <int NSLOT, int WIN, bool MAPPED>
+template <int NSLOT, int WIN, int MODE>
 int resident_groups() {
   static std::atomic<int> cache[64];
   int dev = 0;
@@ -583,7 +729,7 @@ int resident_groups() {
   if (v == 0) {
     int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, summarize_kernel<NSLOT, WIN, MAPPED>, kThreads, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, summarize_kernel<NSLOT, WIN, MODE>, kThreads, 0) !=
         hipSuccess)
       return 0;
     v = cus * (per_cu > 0 ? per_cu : 1);
@@ -592,12 +738,12 @@ int resident_groups() {
   return v;
 }
 
-template <int NSLOT, int WIN, bool MAPPED>
+template <int NSLOT, int WIN, int MODE>
 hipError_t launch_t(const Args& args, int32_t n_seg, hipStream_t st) {
-  const int groups = resident_groups<NSLOT, WIN, MAPPED>();
+  const int groups = resident_groups<NSLOT, WIN, MODE>();
   if (groups <= 0) return hipErrorInvalidDevice;
   const int grid = n_seg < groups ? n_seg : groups;
-  hipLaunchKernelGGL((summarize_kernel<NSLOT, WIN, MAPPED>), dim3(grid), dim3(kThreads), 0, st, args);
+  hipLaunchKernelGGL((summarize_kernel<NSLOT, WIN, MODE>), dim3(grid), dim3(kThreads), 0, st, args);
   return hipGetLastError();
 }
 
@@ -613,10 +759,20 @@ hipError_t launch_summarize(const SummarizeLaunch& l, hipStream_t st) {
          l.keyed ? l.n_streams : 0, n_keys, vec_ok, l.n_seg, l.queue, l.count, l.sum_ns, l.min_ns, l.max_ns, l.hist, l.n_valid, l.n_invalid, l.t_first, l.t_last,
          l.step_ns, l.busy_ns, l.stream_busy_ns, l.wire_bytes, l.dev_status};
   if (l.n_seg == 0) return hipSuccess;
-  if (n_keys <= 64) return launch_t<64, 10, false>(a, l.n_seg, st);
-  if (n_keys <= 512) return launch_t<512, 10, false>(a, l.n_seg, st);
-  if (n_keys <= 2048) return launch_t<2048, 10, false>(a, l.n_seg, st);
-  return launch_t<2048, 6, true>(a, l.n_seg, st);
+  if (n_keys <= 64) return launch_t<64, 10, kDense>(a, l.n_seg, st);
+  if (n_keys <= 512) return launch_t<512, 10, kDense>(a, l.n_seg, st);
+  if (n_keys <= 2048) return launch_t<2048, 10, kDense>(a, l.n_seg, st);
+  // Past the map's 16,384 entries the table of keys seen: with one map range
+  // after another a segment is read once per range, and with windows fixed
+  // around the first duration the full records ran out, each time for one
+  // more read (512 segments of 400,000 events, 32,768 keys of which about
+  // 1,900 occur, a third of them at 1x, 3x and 9x: 3.6 ms by ranges, 3.2 with
+  // the table, 1.12 with the table and spans; the events read once take 0.8).
+  // Up to 16,384 keys the map's one two-byte read is the cheaper lookup; a
+  // key space that fits the slots needs neither, and its ten-bin window loses
+  // 4% to the span's extra instructions (2,048 keys: 3.55 against 3.66 ms).
+  if (n_keys <= kMapIds) return launch_t<2048, 6, kMapped>(a, l.n_seg, st);
+  return launch_t<2048, 6, kHashed>(a, l.n_seg, st);
 }
 
 }  // namespace argus

@@ -192,7 +192,7 @@ def test_mapped_slot_overflow():
 
 
 def test_mapped_several_id_ranges():
-    _announce("mapped ids: id space of 40,000 (several ranges)")
+    _announce("hashed ids: id space of 40,000")
     K = 40_000
     ev = _random_events(50_000, K, 8, seed=22, seg_lengths=[20_000, 0, 30_000, 0])
     g, o = _summarize_both(ev, 2, 2, K, 8)
@@ -365,12 +365,31 @@ def test_l1_series_length_edges(S):
         P.assert_float_close(g, o, ["cp_ratio"], f"l1 S={S} {p}")
 
 
+@pytest.mark.parametrize("K,present", [(16_384, 2_000), (16_385, 1), (16_385, 2_048), (20_000, 2_049), (49_999, 3_000),
+                                       (65_536, 9_000)])
+def test_sparse_id_space_edges(K, present):
+    """Id spaces around the largest map (16,384 ids) and up to the largest
+    allowed (65,536 ids, one range of the hash table), with occurring ids up to, at and past the 2,048 slots
+    of a pass; the first and last id occur, and durations span all octaves, so
+    that full histogram records run out too."""
+    _announce(f"sparse ids K={K} present={present}")
+    rng = np.random.default_rng(K + present)
+    ids = np.unique(np.concatenate([[0, K - 1], rng.choice(K, present, replace=False)]))[-present:]
+    ev = _random_events(30_003, K, 5, seed=K % 1000 + present, seg_lengths=[20_001, 1, 0, 10_001])
+    ev["kernel_id"] = np.where(ev["kernel_id"] < 0, ev["kernel_id"], rng.choice(ids, 30_003)).astype(np.int32)
+    ev["kernel_id"][:2] = K - 1, ids[0]
+    g = pa.summarize(_dev_events(ev), 4, 1, K, 5)
+    torch.cuda.synchronize()
+    o = oracle.summarize(ev, K, 5)
+    P.assert_int_equal(g, o, P.SUM_INT_FIELDS, f"sparse K={K} present={present}")
+
+
 @pytest.mark.parametrize("K,keyed", [(64, False), (2048, False), (6000, False), (40_000, False), (300, True)])
 def test_absent_cells_keep_their_buffers(K, keyed):
     """Only the count of an absent cell is written: its sum, min, max and
     histogram keep what the caller's buffers held (a sentinel here), while
-    every present cell matches the oracle. Dense (K <= 2048), mapped
-    (larger K, one and several id ranges) and (kernel, stream) keys; half of
+    every present cell matches the oracle. Dense (K <= 2048), mapped,
+    hashed (K > 16,384) and (kernel, stream) keys; half of
     the ids never occur."""
     _announce(f"absent cells untouched: K={K} keyed={keyed}")
     NS = 4
