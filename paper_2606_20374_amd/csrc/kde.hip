@@ -47,6 +47,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef long long v2l __attribute__((ext_vector_type(2)));
 
 constexpr int kScatterThreads = 512;
+constexpr int kScatterD = 2;  // groups of four events in flight per thread
 constexpr int kWave = 64;
 constexpr int kMaxC = ARGUS_KDE_MAXC;
 constexpr int kMaxT = 2 * kMaxC;  // selection targets: p50 and p99 per cluster
@@ -184,106 +185,6 @@ __device__ __forceinline__ void wave_sync() {
 
 __device__ __forceinline__ void flag(const KdeArgs& a, int bit) {
   if (a.dev_status) atomicOr(a.dev_status, bit);
-}
-
-// ----------------------------------------------------------------- scatter
-
-struct ScatterCtx {
-  uint32_t* cur;
-  uint64_t* out;
-  uint32_t len;
-  int32_t K, NS;
-};
-
-__device__ __forceinline__ void scatter_one(const ScatterCtx& s, int32_t kid, int32_t st, int64_t t0, int64_t t1) {
-  if (kid >= 0 && kid < s.K && st >= 0 && st < s.NS && t0 >= 0 && t1 >= t0) {
-    const uint32_t p = atomicAdd(&s.cur[kid], 1u);
-    if (p < s.len) s.out[p] = (uint64_t)t1 - (uint64_t)t0;
-  }
-}
-
-__global__ __launch_bounds__(kScatterThreads) void kde_scatter_kernel(KdeArgs a) {
-  __shared__ uint32_t cur[ARGUS_MAX_KDE_KERNELS];
-  __shared__ uint32_t wave_tot[kScatterThreads / kWave];
-  __shared__ uint32_t claim;
-  const int tid = threadIdx.x, K = a.K;
-  const int per = (K + kScatterThreads - 1) / kScatterThreads;
-  const v4i* K4 = reinterpret_cast<const v4i*>(a.kernel_id);
-  const v4i* S4 = reinterpret_cast<const v4i*>(a.stream);
-  const v2l* T0 = reinterpret_cast<const v2l*>(a.start_ns);
-  const v2l* T1 = reinterpret_cast<const v2l*>(a.end_ns);
-  while (true) {
-    if (tid == 0) claim = atomicAdd(&a.counters[0], 1u);
-    __syncthreads();
-    const uint32_t g = claim;
-    if (g >= (uint32_t)a.n_seg) break;
-    if (tid == 0) a.seg_w4[g] = 0;  // 8-byte records
-    // cursors = exclusive prefix of the segment's per-kernel counts
-    const uint32_t* cnt = a.count + (int64_t)g * K;
-    const int k0 = tid * per, k1 = min(K, k0 + per);
-    uint32_t own = 0;
-    for (int k = k0; k < k1; ++k) own += cnt[k];
-    const uint32_t incl = wave_incl_scan(own);
-    if (lane_id() == kWave - 1) wave_tot[tid / kWave] = incl;
-    __syncthreads();
-    uint32_t base = incl - own;
-    for (int w = 0; w < tid / kWave; ++w) base += wave_tot[w];
-    for (int k = k0; k < k1; ++k) {
-      cur[k] = base;
-      base += cnt[k];
-    }
-    __syncthreads();
-    const int64_t lo = a.seg_off[g], hi = a.seg_off[g + 1];
-    const bool bad = !(lo >= 0 && lo <= hi && hi <= a.n_events && hi - lo <= (int64_t)UINT32_MAX);
-    if (!bad) {
-      const ScatterCtx s{cur, a.bucket + lo, (uint32_t)(hi - lo), K, a.NS};
-      int64_t a4 = hi, b4 = hi;  // aligned body [a4, b4) in groups of four events
-      if (a.vec_ok) {
-        const int64_t up = (lo + 3) & ~(int64_t)3, dn = hi & ~(int64_t)3;
-        a4 = up < hi ? up : hi;
-        b4 = dn > a4 ? dn : a4;
-      }
-      // head [lo, a4) (the whole segment without aligned arrays) and tail [b4, hi)
-      for (int64_t i = lo + tid; i < a4; i += kScatterThreads)
-        scatter_one(s, a.kernel_id[i], a.stream[i], a.start_ns[i], a.end_ns[i]);
-      for (int64_t i = b4 + tid; i < hi; i += kScatterThreads)
-        scatter_one(s, a.kernel_id[i], a.stream[i], a.start_ns[i], a.end_ns[i]);
-      const int64_t qb = b4 >> 2;
-      int64_t q = (a4 >> 2) + tid;
-      v4i nk4 = 0, ns4 = 0;
-      v2l na0 = 0, na1 = 0, nb0 = 0, nb1 = 0;
-      if (q < qb) {
-        nk4 = __builtin_nontemporal_load(K4 + q);
-        ns4 = __builtin_nontemporal_load(S4 + q);
-        na0 = __builtin_nontemporal_load(T0 + 2 * q);
-        na1 = __builtin_nontemporal_load(T0 + 2 * q + 1);
-        nb0 = __builtin_nontemporal_load(T1 + 2 * q);
-        nb1 = __builtin_nontemporal_load(T1 + 2 * q + 1);
-      }
-      while (q < qb) {
-        const v4i k4 = nk4, s4 = ns4;
-        const v2l x0 = na0, x1 = na1, y0 = nb0, y1 = nb1;
-        const int64_t qn = q + kScatterThreads;
-        if (qn < qb) {
-          nk4 = __builtin_nontemporal_load(K4 + qn);
-          ns4 = __builtin_nontemporal_load(S4 + qn);
-          na0 = __builtin_nontemporal_load(T0 + 2 * qn);
-          na1 = __builtin_nontemporal_load(T0 + 2 * qn + 1);
-          nb0 = __builtin_nontemporal_load(T1 + 2 * qn);
-          nb1 = __builtin_nontemporal_load(T1 + 2 * qn + 1);
-        }
-        scatter_one(s, k4.x, s4.x, x0.x, y0.x);
-        scatter_one(s, k4.y, s4.y, x0.y, y0.y);
-        scatter_one(s, k4.z, s4.z, x1.x, y1.x);
-        scatter_one(s, k4.w, s4.w, x1.y, y1.y);
-        q = qn;
-      }
-    }
-    __syncthreads();
-    uint32_t* ends = a.cell_end + (int64_t)g * K;
-    for (int k = tid; k < K; k += kScatterThreads) ends[k] = cur[k];
-    __syncthreads();
-  }
 }
 
 // ----------------------------------------------------------- staged scatter
@@ -669,6 +570,148 @@ __global__ __launch_bounds__(kStageThreads) void kde_scatter_staged_kernel(KdeAr
     lds_barrier();
     uint32_t* ends = a.cell_end + (int64_t)g * K;
     for (int k = tid; k < K; k += kStageThreads) ends[k] = cur[k];
+    lds_barrier();
+  }
+}
+
+// ----------------------------------------------------------- direct scatter
+// For larger id spaces, whose windows would not fit the LDS: every duration
+// goes to its place with its own store. Bound by memory instructions in
+// flight, not by bytes: behind conditional stores the compiler waits for all
+// of them before it uses the next group's loads, so segments of up to
+// kBufEvents events take the staged scatter's form (idle lanes store out of
+// range, four cursors taken at once) and its record widths
+// (1,024 rank-steps of 200,000 events over 8,200 ids, nine in ten on eight
+// of them: 2,178 us with conditional 8-byte stores, 1,744 us so).
+struct ScatterCtx {
+  uint32_t* cur;
+  uint32_t len;
+  int32_t K, NS;
+};
+
+template <typename R>
+__device__ __forceinline__ void scatter_one(const ScatterCtx& s, R* out, int32_t kid, int32_t st, int64_t t0,
+                                            int64_t t1) {
+  if (kid >= 0 && kid < s.K && st >= 0 && st < s.NS && t0 >= 0 && t1 >= t0) {
+    const uint32_t p = atomicAdd(&s.cur[kid], 1u);
+    if (p < s.len) out[p] = to_record<R>((uint64_t)t1 - (uint64_t)t0);
+  }
+}
+
+// The aligned body of a segment of at most kBufEvents events: ng groups of
+// four from event a4 on. Cursor ARGUS_MAX_KDE_KERNELS is the spare slot.
+template <typename R>
+__device__ void scatter_body(const KdeArgs& a, const ScatterCtx& s, R* out, int64_t a4, int64_t ng, int tid) {
+  const __amdgpu_buffer_rsrc_t rk = buf_rsrc(a.kernel_id + a4, ng * 16), rs = buf_rsrc(a.stream + a4, ng * 16);
+  const __amdgpu_buffer_rsrc_t r0 = buf_rsrc(a.start_ns + a4, ng * 32), r1 = buf_rsrc(a.end_ns + a4, ng * 32);
+  const __amdgpu_buffer_rsrc_t ro = buf_rsrc(out, (int64_t)s.len * (int64_t)sizeof(R));
+  v4u bk[kScatterD], bs[kScatterD], ba0[kScatterD], ba1[kScatterD], bb0[kScatterD], bb1[kScatterD];
+  auto load = [&](int d, int64_t rq) {
+    const uint32_t o16 = rq < ng ? (uint32_t)rq * 16u : kOob, o32 = rq < ng ? (uint32_t)rq * 32u : kOob;
+    bk[d] = __builtin_amdgcn_raw_buffer_load_b128(rk, (int)o16, 0, 0);
+    bs[d] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o16, 0, 0);
+    ba0[d] = __builtin_amdgcn_raw_buffer_load_b128(r0, (int)o32, 0, 0);
+    ba1[d] = __builtin_amdgcn_raw_buffer_load_b128(r0, (int)(o32 + 16u), 0, 0);
+    bb0[d] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)o32, 0, 0);
+    bb1[d] = __builtin_amdgcn_raw_buffer_load_b128(r1, (int)(o32 + 16u), 0, 0);
+  };
+#pragma unroll
+  for (int d = 0; d < kScatterD; ++d) load(d, tid + (int64_t)d * kScatterThreads);
+  for (int64_t rb = 0; rb < ng; rb += (int64_t)kScatterD * kScatterThreads) {
+#pragma unroll
+    for (int d = 0; d < kScatterD; ++d) {
+      const int64_t rq = rb + tid + (int64_t)d * kScatterThreads;
+      const v4i k4 = __builtin_bit_cast(v4i, bk[d]), s4 = __builtin_bit_cast(v4i, bs[d]);
+      const v2l x0 = __builtin_bit_cast(v2l, ba0[d]), x1 = __builtin_bit_cast(v2l, ba1[d]);
+      const v2l y0 = __builtin_bit_cast(v2l, bb0[d]), y1 = __builtin_bit_cast(v2l, bb1[d]);
+      load(d, rq + (int64_t)kScatterD * kScatterThreads);
+      const int32_t kid[4] = {k4.x, k4.y, k4.z, k4.w}, st[4] = {s4.x, s4.y, s4.z, s4.w};
+      const int64_t t0[4] = {x0.x, x0.y, x1.x, x1.y}, t1[4] = {y0.x, y0.y, y1.x, y1.y};
+      bool val[4];
+      uint32_t p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        val[i] = rq < ng && kid[i] >= 0 && kid[i] < s.K && st[i] >= 0 && st[i] < s.NS && t0[i] >= 0 && t1[i] >= t0[i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = atomicAdd(&s.cur[val[i] ? kid[i] : ARGUS_MAX_KDE_KERNELS], 1u);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        buf_store(ro, val[i] && p[i] < s.len ? p[i] * (uint32_t)sizeof(R) : kOob,
+                  to_record<R>((uint64_t)t1[i] - (uint64_t)t0[i]));
+    }
+  }
+}
+
+template <typename R>
+__device__ void scatter_segment(const KdeArgs& a, const ScatterCtx& s, int64_t lo, int64_t hi, int tid) {
+  R* out = reinterpret_cast<R*>(a.bucket + lo);
+  int64_t a4 = hi, b4 = hi;  // aligned body [a4, b4) in groups of four events
+  if (a.vec_ok && hi - lo <= kBufEvents) {
+    const int64_t up = (lo + 3) & ~(int64_t)3, dn = hi & ~(int64_t)3;
+    a4 = up < hi ? up : hi;
+    b4 = dn > a4 ? dn : a4;
+  }
+  // head [lo, a4) (the whole segment without aligned arrays, or longer than
+  // 32-bit offsets reach) and tail [b4, hi)
+  for (int64_t i = lo + tid; i < a4; i += kScatterThreads)
+    scatter_one(s, out, a.kernel_id[i], a.stream[i], a.start_ns[i], a.end_ns[i]);
+  for (int64_t i = b4 + tid; i < hi; i += kScatterThreads)
+    scatter_one(s, out, a.kernel_id[i], a.stream[i], a.start_ns[i], a.end_ns[i]);
+  if (b4 > a4) scatter_body<R>(a, s, out, a4, (b4 - a4) >> 2, tid);
+}
+
+__global__ __launch_bounds__(kScatterThreads) void kde_scatter_kernel(KdeArgs a) {
+  __shared__ uint32_t cur[ARGUS_MAX_KDE_KERNELS + 1];  // + the spare slot
+  __shared__ uint32_t wave_tot[kScatterThreads / kWave];
+  __shared__ uint32_t claim, wide;
+  const int tid = threadIdx.x, K = a.K;
+  const int per = (K + kScatterThreads - 1) / kScatterThreads;
+  while (true) {
+    if (tid == 0) {
+      claim = atomicAdd(&a.counters[0], 1u);
+      wide = 0;
+    }
+    __syncthreads();
+    const uint32_t g = claim;
+    if (g >= (uint32_t)a.n_seg) break;
+    // cursors = exclusive prefix of the segment's per-kernel counts; any
+    // present cell's maximum at or above kW4Lim asks for 8-byte records
+    const uint32_t* cnt = a.count + (int64_t)g * K;
+    const int64_t* mx = a.max_ns + (int64_t)g * K;
+    bool big = false;
+    for (int k = tid; k < K; k += kScatterThreads) {
+      const uint32_t n = cnt[k];
+      cur[k] = n;
+      big |= n != 0 && (uint64_t)mx[k] >= kW4Lim;
+    }
+    if (__any(big) && lane_id() == 0) wide = 1;
+    __syncthreads();
+    const int k0 = tid * per, k1 = min(K, k0 + per);
+    uint32_t own = 0;
+    for (int k = k0; k < k1; ++k) own += cur[k];
+    const uint32_t incl = wave_incl_scan(own);
+    if (lane_id() == kWave - 1) wave_tot[tid / kWave] = incl;
+    __syncthreads();
+    uint32_t base = incl - own;
+    for (int w = 0; w < tid / kWave; ++w) base += wave_tot[w];
+    for (int k = k0; k < k1; ++k) {
+      const uint32_t n = cur[k];
+      cur[k] = base;
+      base += n;
+    }
+    __syncthreads();
+    const int64_t lo = a.seg_off[g], hi = a.seg_off[g + 1];
+    const bool bad = !(lo >= 0 && lo <= hi && hi <= a.n_events && hi - lo <= (int64_t)UINT32_MAX);
+    const bool w4 = !bad && hi - lo <= kBufEvents && !wide;
+    if (tid == 0) a.seg_w4[g] = w4 ? 1 : 0;
+    if (!bad) {
+      const ScatterCtx s{cur, (uint32_t)(hi - lo), K, a.NS};
+      if (w4) scatter_segment<uint32_t>(a, s, lo, hi, tid);
+      else scatter_segment<uint64_t>(a, s, lo, hi, tid);
+    }
+    lds_barrier();
+    uint32_t* ends = a.cell_end + (int64_t)g * K;
+    for (int k = tid; k < K; k += kScatterThreads) ends[k] = cur[k];
     lds_barrier();
   }
 }

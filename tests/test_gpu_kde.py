@@ -330,6 +330,47 @@ def test_kde_record_widths_mixed():
     P.assert_kde_equal(k2, {f: np.asarray(o[f])[keep] for f in P.KDE_FIELDS}, "understated maximum", rows=keep)
 
 
+@pytest.mark.parametrize("K,aligned", [(2049, True), (2049, False), (16_384, True)])
+def test_kde_direct_scatter_record_widths(K, aligned):
+    """Id spaces past the staged scatter: 4-byte and 8-byte segments, odd
+    segment starts, an empty one, invalid records, the last kernel id, and a
+    summary that understates a maximum."""
+    _announce(f"kde direct scatter, K={K} aligned={aligned}")
+    rng = np.random.default_rng(K)
+    tops, lens = [2**31 - 1, 2**31, 5, 2**33], [20_003, 4097, 0, 1]
+    kid, d = [], []
+    for top, n in zip(tops, lens):
+        ids = np.concatenate([[K - 1], rng.integers(0, K, 90)])
+        k = np.where(rng.random(n) < 0.8, K // 2, rng.choice(ids, n))
+        v = np.exp(rng.normal(np.log(3e4), 0.3, n)).astype(np.int64)
+        if n:
+            k[0], v[0] = K - 1, top
+        kid.append(k)
+        d.append(v)
+    kid, d = np.concatenate(kid).astype(np.int32), np.concatenate(d)
+    n = len(kid)
+    t0 = rng.integers(0, 2**40, n)
+    st = (kid % 3).astype(np.int32)
+    bad = rng.random(n) < 0.01
+    bad[[0, 20_003, n - 1]] = False
+    st[bad] = 3
+    ev = {"kernel_id": kid, "stream": st, "start_ns": t0, "end_ns": t0 + d,
+          "seg_off": np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)}
+    ev_d = _dev(ev) if aligned else _dev_unaligned(ev)
+    s = pa.summarize(ev_d, 2, 2, K, 3)
+    k = pa.kde(ev_d, s, 2, 2, K, 3)
+    torch.cuda.synchronize()
+    assert int(k["dev_status"].item()) == 0
+    P.assert_kde_equal(k, oracle.kde(ev, K, 3), f"direct scatter K={K}", rows=np.arange(4 * K))
+    assert list(_record_widths(k, n, 4, 4 * K)) == [1, 0, 1, 0]
+    s["max_ns"][K + K - 1] = 2**31 - 1
+    k = pa.kde(ev_d, s, 2, 2, K, 3)
+    torch.cuda.synchronize()
+    assert int(k["dev_status"].item()) == pa.argus.DEV_KDE_SUMMARY
+    assert list(_record_widths(k, n, 4, 4 * K)) == [1, 1, 1, 0]
+    assert int(k["n_clusters"][2 * K - 1].item()) == 0
+
+
 def test_kde_long_segment_global_path():
     """A rank-step of more than 2^26 events is scattered with global loads and
     8-byte records (the buffer path covers shorter ones); with the stream
