@@ -81,13 +81,13 @@ __device__ void select_ranks(const KeyT (&key)[V], uint64_t vm, uint64_t range, 
       }
 #pragma unroll
       for (int j = 0; j < V; ++j) {
-        const uint64_t kj = (uint64_t)key[j];
+        const KeyT kj = key[j];  // shifts and compares at the key's own width
         const bool ok = (vm >> j) & 1u;
         const uint32_t digit = (uint32_t)(kj >> shift) & (uint32_t)(NB - 1);
-        const uint64_t hi = top || shift + DB >= 64 ? 0 : kj >> (shift + DB);
+        const KeyT hi = top || shift + DB >= (int)sizeof(KeyT) * 8 ? 0 : kj >> (shift + DB);
 #pragma unroll
         for (int t = 0; t < T; ++t)
-          if (rep[t] == t) hist_add<HR>(sh.hist[t], digit, ok && (top || hi == prefix[t]));
+          if (rep[t] == t) hist_add<HR>(sh.hist[t], digit, ok && (top || hi == (KeyT)prefix[t]));
       }
       __syncthreads();
       // per-target inclusive scan over the bins, BPT consecutive bins per

@@ -309,6 +309,25 @@ def test_cross_rank_quotient_paths():
     _xr_both(cnt.reshape(-1).astype(np.uint32), sm.reshape(-1).astype(np.int64), R, 1, K)
 
 
+@pytest.mark.parametrize("R", [5, 300, 7000])
+@pytest.mark.parametrize("params", [{}, dict(k_mad_pm=2**31 - 1, ratio_pm=2**31 - 1, alpha_pm=2**31 - 1),
+                                    dict(k_mad_pm=0, ratio_pm=0, alpha_pm=0)])
+def test_cross_rank_word_widths(R, params):
+    """Means on both sides of 2^32 ns and spans of 2^32 - 1, 2^32 and
+    2^32 + 1 between the smallest and the largest: 32- and 64-bit keys and
+    comparisons, with the largest and smallest parameters."""
+    _announce(f"cross-rank word widths R={R} {params}")
+    rng = np.random.default_rng(R)
+    spans = [2**31 - 1, 2**32 - 1, 2**32, 2**32 + 1, 1, 2**43]
+    lows = [0, 5, 2**32 - 3, 2**33]
+    x = np.stack([lo + rng.integers(0, sp + 1, R) for sp in spans for lo in lows], axis=1)
+    x[0], x[1] = [lo for sp in spans for lo in lows], [lo + sp for sp in spans for lo in lows]
+    x[rng.random(x.shape) < 0.05] = -1
+    x[:2] = np.abs(x[:2])
+    cnt, sm = _from_x(x)
+    _xr_both(cnt, sm, R, 1, x.shape[1], **params)
+
+
 # ------------------------------------------------------------------- L1
 def test_l1_golden_and_random():
     _announce("L1 golden + random")
