@@ -119,7 +119,7 @@ constexpr int kKeep = 24;    // members of a wavefront whose means stay in LDS b
 constexpr int kSmall = 32;   // listed members up to which a group is small (one wavefront)
 constexpr int kBatch = 8;    // members whose cells are loaded together
 constexpr double kBand = 1e-12;  // of the double comparisons below (their error is below 1e-14)
-constexpr uint32_t kNoMean = 0xFFFFFFFFu;
+constexpr uint32_t kNoMean = 0xFFFFFFFFu;  // no mean that is kept: those lie below it
 
 // x = floor(sum / n) for n >= 1 (sum read as uint64), or -1 when x is out of
 // the domain. The double quotient is within x 2^-51 of the real one, so below
@@ -193,16 +193,16 @@ __device__ __forceinline__ bool sum_part(const L2Args& a, const Part& p, Sums& t
       uint32_t row[kBatch], cnt[kBatch];
       int64_t sm[kBatch];
       p.load(a, todo, m, row, cnt, sm);
-      // means below 2^32 of sums below 2^53: both operands are exact doubles,
-      // so the floor of the rounded quotient is exact or one above, and the
-      // squares fit 64 bits
+      // means below kNoMean of sums below 2^53: both operands are exact
+      // doubles, so the floor of the rounded quotient is exact or one above,
+      // and the squares fit 64 bits
       Sums q = t;
       bool wide = false;
       const bool room = at + kBatch <= kKeep;
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const double nd = (double)cnt[u], sd = (double)(uint64_t)sm[u], qd = sd / nd;
-        wide = wide || (cnt[u] != 0 && !(sd < 0x1p53 && qd < 0x1p32));
+        wide = wide || (cnt[u] != 0 && !(sd < 0x1p53 && qd < (double)kNoMean));
         uint32_t x = (uint32_t)qd;
         x -= fma(-(double)x, nd, sd) < 0.0 ? 1u : 0u;
         x = cnt[u] ? x : 0u;

@@ -149,3 +149,17 @@ def test_l2_group_size_edges(size, E, scale):
     off = np.tile(np.arange(G + 1, dtype=np.int32) * size, (2, 1))
     mem = np.stack([rng.permutation(R), np.arange(R)]).astype(np.int32)
     _both(cnt, sm, R, S, E, route, off, mem, f"size {size} E {E} scale {scale}", z_pm=1500)
+
+
+@pytest.mark.parametrize("size", [3, 12, 40])
+@pytest.mark.parametrize("mean", [2**32 - 2, 2**32 - 1, 2**32])
+def test_l2_means_around_32_bits(size, mean):
+    """A member's mean at the largest 32-bit values and one past them, in small
+    and large groups, as the one outlier (a straggler from 12 members on) and
+    as every member's."""
+    _announce(f"l2 mean {mean} in a group of {size}")
+    xs = 1000 + np.arange(size, dtype=np.int64)
+    xs[size // 2] = mean
+    g, _ = _one_group(xs, f"one member at {mean}")
+    assert int(P.to_np(g["flags"])[size // 2]) == (3 if size > 11 else 1)
+    _one_group(np.full(size, mean, np.int64), f"all members at {mean}")
