@@ -179,8 +179,9 @@ struct Sums {
   u128 Q;
 };
 
-// Exact sums over a part's present members; their means go to keep (row u of
-// 64 lanes: member u) while they fit. Returns whether keep holds all of them.
+// Exact sums over a part's present members; their means go to keep (a row of
+// 64 lanes per member, every 64 listings' rows from a multiple of kBatch on)
+// while they fit. Returns whether keep holds all of them.
 __device__ __forceinline__ bool sum_part(const L2Args& a, const Part& p, Sums& t, uint32_t (*keep)[64], bool& dom) {
   const int lane = threadIdx.x & 63;
   t = Sums{0, 0, 0};
@@ -329,6 +330,7 @@ __device__ __forceinline__ uint32_t write_part(const L2Args& a, const Part& p, c
         const uint32_t x = keep[at++][lane];
         if (on && x != kNoMean) ns += g.write(a, row, p.e, (double)x, x);
       }
+      at = (at + kBatch - 1) / kBatch * kBatch;
     }
     while (todo) {
       uint32_t row[kBatch], cnt[kBatch];

@@ -163,3 +163,29 @@ def test_l2_means_around_32_bits(size, mean):
     g, _ = _one_group(xs, f"one member at {mean}")
     assert int(P.to_np(g["flags"])[size // 2]) == (3 if size > 11 else 1)
     _one_group(np.full(size, mean, np.int64), f"all members at {mean}")
+
+
+@pytest.mark.parametrize("filler", ["invalid", "duplicate"])
+@pytest.mark.parametrize("listings,valid", [(600, 1), (600, 10), (1024, 5), (1024, 20), (2100, 13), (4096, 9)])
+def test_l2_sparse_listings(listings, valid, filler):
+    """A group of many listings of which few count: the rest are ids that are
+    skipped or second listings. A wavefront's share (an eighth) spans several
+    of its 64-listing chunks, each with a few members that count, which fit
+    what it keeps between its two passes."""
+    _announce(f"l2 {listings} listings, {valid} valid per share, filler {filler}")
+    rng = np.random.default_rng(listings * 31 + valid)
+    R, S, E = listings, 1, 70
+    mem = np.full(R, -1, np.int32)
+    ids = rng.permutation(R)
+    n = 0
+    for w in range(8):
+        lo, hi = R * w // 8, R * (w + 1) // 8
+        for i in np.sort(rng.choice(np.arange(lo, hi), size=valid, replace=False)):
+            mem[i] = ids[n]
+            n += 1
+    if filler == "duplicate":
+        mem[mem < 0] = mem[mem >= 0][0]
+    cnt = rng.integers(0, 4, size=R * S * E).astype(np.uint32)
+    sm = rng.integers(10**5, 10**6, size=R * S * E) * cnt.astype(np.int64)
+    _both(cnt, sm, R, S, E, np.zeros(E, np.uint8), np.array([[0, R]], np.int32), mem.reshape(1, R),
+          f"{listings} listings, {valid} valid, {filler}", z_pm=1500)
