@@ -307,7 +307,8 @@ struct Group {
   __device__ __forceinline__ uint32_t write(const L2Args& a, uint32_t row, int e, double xd, uint64_t x) const {
     const bool f = straggler(a, xd, x);
     const uint64_t c = (uint64_t)row * (uint32_t)a.E;
-    (a.o.z + c)[(uint32_t)e] = (float)over_sd(xd - mean);
+    // + 0: sd 0 makes a mean that is rounded above x a negative zero, and no other quotient rounds to one
+    (a.o.z + c)[(uint32_t)e] = (float)over_sd(xd - mean) + 0.0f;
     (a.o.flags + c)[(uint32_t)e] = f ? 3 : 1;
     return f ? 1u : 0u;
   }

@@ -189,3 +189,13 @@ def test_l2_sparse_listings(listings, valid, filler):
     sm = rng.integers(10**5, 10**6, size=R * S * E) * cnt.astype(np.int64)
     _both(cnt, sm, R, S, E, np.zeros(E, np.uint8), np.array([[0, R]], np.int32), mem.reshape(1, R),
           f"{listings} listings, {valid} valid, {filler}", z_pm=1500)
+
+
+@pytest.mark.parametrize("n,x", [(12, 2**40 - 3), (21831, 949394193386), (54702, 1073001553514)])
+def test_l2_equal_members_have_positive_zero(n, x):
+    """Equal members have std 0 and z = +0, also where the sum passes 2^53 and
+    the double mean rounds to one side of them."""
+    _announce(f"l2 {n} equal members of {x}")
+    g, _ = _one_group(np.full(n, x, np.int64), f"{n} x {x}")
+    z = P.to_np(g["z"])
+    assert not z.any() and not np.signbit(z).any()
