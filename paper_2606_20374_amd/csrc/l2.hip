@@ -356,7 +356,6 @@ struct SmallOut {
 struct LargePart {
   uint64_t S[kWaves][64], Qlo[kWaves][64], Qhi[kWaves][64];
   uint32_t n[kWaves][64];
-  uint32_t ns[64];
 };
 
 // Workgroup (x, y, z): z names a step and a dimension d, y a span of kWaves
@@ -378,6 +377,9 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
     SmallOut small;
     LargePart large;
   } sh;
+  // apart from the union: the first wavefront reads a large group's stragglers
+  // while others may have gone on to the next events' small groups
+  __shared__ uint32_t ns_sh[64];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = (int)(blockIdx.z / (uint32_t)a.n_dims), d = (int)(blockIdx.z % (uint32_t)a.n_dims);
   const int slot = (int)blockIdx.y / n_span, g0 = (int)blockIdx.y % n_span * kWaves;
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
           sh.large.S[w][lane] = t.S;
           sh.large.Qlo[w][lane] = (uint64_t)t.Q;
           sh.large.Qhi[w][lane] = (uint64_t)(t.Q >> 64);
-          if (w == 0) sh.large.ns[lane] = 0;
+          if (w == 0) ns_sh[lane] = 0;
           lds_barrier();
           t = Sums{0, 0, 0};
 #pragma unroll 1
@@ -464,12 +466,12 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
           gr.set(a, t);
           const uint32_t ns = write_part(a, p, gr, on && gr.eval, kept, keep_sh[w]);
           if (large) {
-            if (ns) atomicAdd(&sh.large.ns[lane], ns);
+            if (ns) atomicAdd(&ns_sh[lane], ns);
             lds_barrier();
             if (w == 0 && on) {
               const int64_t go = ((int64_t)s * a.E + p.e) * a.max_groups + g0 + j;
               a.o.n[go] = t.n;
-              a.o.n_strag[go] = sh.large.ns[lane];
+              a.o.n_strag[go] = ns_sh[lane];
               a.o.mean_ns[go] = gr.mean;
               a.o.std_ns[go] = gr.sd;
               a.o.cv[go] = gr.cv;

@@ -199,3 +199,19 @@ def test_l2_equal_members_have_positive_zero(n, x):
     g, _ = _one_group(np.full(n, x, np.int64), f"{n} x {x}")
     z = P.to_np(g["z"])
     assert not z.any() and not np.signbit(z).any()
+
+
+@pytest.mark.parametrize("E", [1100, 2048, 4100])
+def test_l2_mixed_sizes_one_dimension(E):
+    """Small and large groups side by side in a span of eight, and so many
+    events of one dimension among 2,048 ids that a workgroup takes several
+    shares of 64 of them one after another."""
+    _announce(f"l2 mixed group sizes, {E} events of one dimension")
+    rng = np.random.default_rng(E)
+    sizes = [8, 40, 200, 3, 33, 1, 64, 5, 32, 100, 2, 48, 6, 7, 90, 12, 34]
+    R, S = sum(sizes), 1
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32).reshape(1, -1)
+    cnt = rng.integers(0, 4, size=R * S * E).astype(np.uint32)
+    sm = rng.integers(10**5, 10**6, size=R * S * E) * cnt.astype(np.int64)
+    _both(cnt, sm, R, S, E, np.zeros(E, np.uint8), off, rng.permutation(R).astype(np.int32).reshape(1, R),
+          f"mixed sizes, E {E}", z_pm=1500)
