@@ -37,6 +37,7 @@
 #include <atomic>
 
 #include "argus_internal.h"
+#include "summarize_hash.h"
 
 namespace argus {
 namespace {
@@ -58,11 +59,6 @@ constexpr int kMapIds = 16384;  // ids in mapped mode
 // exit (and report) in that case instead of hanging.
 constexpr int kSpinCap = 1 << 16;
 constexpr int kMaxStuckPasses = 4;
-// Hashed mode: 2,048 buckets of four entries (one 16-byte LDS read), at most
-// a quarter full, so all but about 0.5% of the keys lie in their own bucket.
-constexpr int kHashIds = ARGUS_MAX_KERNELS;  // every key space is one range in hashed mode
-constexpr int kHash = 8192, kBucketShift = 32 - 11;
-constexpr uint32_t kHashEmpty = 0xFFFFFFFFu, kTagBits = 12, kTagMask = 0xFFF, kTagBusy = 0xFFE, kTagDefer = 0xFFD;
 constexpr int kDense = 0, kMapped = 1, kHashed = 2;
 constexpr uint32_t kMapEmpty = 0xFFFF, kMapBusy = 0xFFFE, kMapDefer = 0xFFFD, kMapDone = 0xFFFC;
 
@@ -73,12 +69,7 @@ constexpr uint32_t kMapEmpty = 0xFFFF, kMapBusy = 0xFFFE, kMapDefer = 0xFFFD, kM
 //
 // map entry (mapped mode, 16 bits, two per 32-bit word): a slot index, or
 // empty / being claimed / deferred to another pass / already written.
-//
-// hash entry (hashed mode, 32 bits): local id << 12 | slot index, or being
-// claimed / deferred in the slot's place; empty is all ones. The table is
-// filled afresh in every pass; ids already written have their bit in done.
-
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+// The hash table of hashed mode: summarize_hash.h.
 
 template <int NSLOT, int WIN, int MODE>
 struct Smem {
@@ -188,79 +179,17 @@ struct Seg {
     return res;
   }
 
-  __device__ __forceinline__ static int hash_bucket(int lk) {
-    return (int)(((uint32_t)lk * 0x9E3779B1u) >> kBucketShift);
-  }
-
-  // The slot of lk if its own bucket e holds it; else -2.
-  __device__ __forceinline__ static int hash_find(int lk, const v4u& e) {
-    int r = -2;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t s = e[i] ^ ((uint32_t)lk << kTagBits);  // below NSLOT only for lk's published entry
-      r = s < (uint32_t)NSLOT ? (int)s : r;
+  // Memory operations of hash_claim.
+  struct LdsOps {
+    __device__ __forceinline__ uint32_t load(const uint32_t* p) const { return lds_load(p); }
+    __device__ __forceinline__ void store(uint32_t* p, uint32_t v) const { lds_store(p, v); }
+    __device__ __forceinline__ uint32_t cas(uint32_t* p, uint32_t expect, uint32_t want) const {
+      return atomicCAS(p, expect, want);
     }
-    return r;
-  }
-
-  // Slot of local id lk, which its bucket (read as e) does not hold with a
-  // slot: claims the first empty entry from the bucket on, or finds the id
-  // further on; -1 when the id is already written or has no slot in this
-  // pass. Entries only go from empty to claimed to published, so the stale
-  // read e can only start the walk early. At most NSLOT ids and one more per
-  // thread are inserted, so the walk always meets an empty entry. Same exit
-  // discipline as map_claim.
-  __device__ int hash_claim(int lk, const v4u& e0) {
-    int res = (sm.done[lk >> 5] >> (lk & 31)) & 1u ? -1 : -2;
-    const uint32_t mine = (uint32_t)lk << kTagBits;
-    int skip = 4;
-#pragma unroll
-    for (int i = 3; i >= 0; --i) skip = e0[i] == kHashEmpty || (e0[i] & ~kTagMask) == mine ? i : skip;
-    int pos = (hash_bucket(lk) * 4 + skip) & (kHash - 1);
-    for (int it = 0;; ++it) {
-      if (res == -2 && it >= kSpinCap) {
-        lds_store(&sm.stuck, 1u);
-        res = -1;
-      }
-      if (res == -2) {
-        uint32_t e = lds_load(&sm.map[pos]);
-        if (e == kHashEmpty) {
-          if (lds_load(&sm.nslots) >= (uint32_t)NSLOT) {
-            lds_store(&sm.poison, 1u);
-            res = -1;
-          } else {
-            e = atomicCAS(&sm.map[pos], kHashEmpty, mine | kTagBusy);
-            if (e == kHashEmpty) {
-              const uint32_t s = atomicAdd(&sm.nslots, 1u);
-              uint32_t tag = kTagDefer;
-              if (s < (uint32_t)NSLOT) {
-                sm.slot_kid[s] = (uint16_t)lk;
-                tag = s;
-                res = (int)s;
-              } else {
-                lds_store(&sm.poison, 1u);
-                res = -1;
-              }
-              lds_store(&sm.map[pos], mine | tag);
-            }
-          }
-        }
-        if (res == -2 && e != kHashEmpty) {
-          if ((e & ~kTagMask) != mine) {
-            pos = (pos + 1) & (kHash - 1);
-          } else {
-            const uint32_t tag = e & kTagMask;
-            if (tag < (uint32_t)NSLOT)
-              res = (int)tag;
-            else if (tag == kTagDefer)
-              res = -1;
-          }
-        }
-      }
-      if (!__any(res == -2)) break;
-    }
-    return res;
-  }
+    __device__ __forceinline__ uint32_t add(uint32_t* p, uint32_t v) const { return atomicAdd(p, v); }
+    __device__ __forceinline__ void order() const { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local"); }
+    __device__ __forceinline__ bool any(bool pending) const { return __any(pending); }
+  };
 
   // Count bin b outside the inline window in a full pool record, claiming
   // one for the slot on first need (same exit discipline as map_claim).
@@ -414,11 +343,14 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& 
       v4u e[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        e[j] = *reinterpret_cast<const v4u*>(&sg.sm.map[sg.hash_bucket(lk[h + j] >= 0 ? lk[h + j] : 0) * 4]);
+        e[j] = *reinterpret_cast<const v4u*>(&sg.sm.map[hash_bucket(lk[h + j] >= 0 ? lk[h + j] : 0) * 4]);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        slot[j] = lk[h + j] >= 0 ? sg.hash_find(lk[h + j], e[j]) : -1;
-        if (slot[j] == -2) slot[j] = sg.hash_claim(lk[h + j], e[j]);
+        slot[j] = lk[h + j] >= 0 ? hash_find<NSLOT>(lk[h + j], e[j]) : -1;
+        if (slot[j] == -2) {
+          typename Seg<NSLOT, WIN, MODE>::LdsOps ops;
+          slot[j] = hash_claim<NSLOT>(ops, sg.sm, lk[h + j], e[j], kSpinCap);
+        }
       }
     } else if (MODE == kMapped) {
       uint32_t e[2];

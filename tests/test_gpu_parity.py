@@ -430,3 +430,24 @@ def test_absent_cells_keep_their_buffers(K, keyed):
         per = P.NB if f == "hist" else 1
         got = P.to_np(g[f]).reshape(cells, per)[absent]
         assert (got == v).all(), (f, "an absent cell's field was written")
+
+
+@pytest.mark.parametrize("K", [6000, 20_000, 65_536])
+def test_sparse_ids_in_runs(K):
+    """Events in runs of one id, 2,100 ids to a segment: when the 2,048 slots
+    run out, many wavefronts claim the same new id at once (mapped and hashed
+    id spaces)."""
+    _announce(f"ids in runs K={K}")
+    rng = np.random.default_rng(K)
+    kid, lens = [], []
+    for _ in range(12):
+        runs = rng.integers(64, 600, 2100)
+        kid.append(np.repeat(rng.choice(K, 2100, replace=False), runs))
+        lens.append(int(runs.sum()))
+    n = sum(lens)
+    ev = _random_events(n, K, 5, seed=K, seg_lengths=lens)
+    ev["kernel_id"] = np.concatenate(kid).astype(np.int32)
+    g = pa.summarize(_dev_events(ev), len(lens), 1, K, 5)
+    torch.cuda.synchronize()
+    o = oracle.summarize(ev, K, 5)
+    P.assert_int_equal(g, o, P.SUM_INT_FIELDS, f"runs K={K}")
