@@ -5,8 +5,8 @@
 //
 // Launches, in order:
 //   compact_clear   the segments' states and the ticket counter.
-//   compact_kernel  one workgroup per segment (a wavefront per segment of up to
-//                   512 cells), in ticket order: each wavefront builds
+//   compact_kernel  one to eight wavefronts per segment, eight to a workgroup,
+//                   in ticket order: each wavefront builds
 //                   the records of a contiguous range of cells in its own LDS
 //                   region, reading every summary field once; the
 //                   segment's size is published, the sizes of the segments
@@ -211,8 +211,10 @@ __device__ __forceinline__ void copy_out(const CompactArgs& a, const uint8_t* re
   if ((uint32_t)lane < tail) dst[head + 4 * words + lane] = region[head + 4 * words + lane];
 }
 
-// kOwn: every wavefront takes a segment of its own, else they share one.
-template <int kWaves, bool kOwn>
+constexpr int kWaves = 8;  // wavefronts of a workgroup
+
+// kShare wavefronts share a segment: a workgroup takes kWaves / kShare of them.
+template <int kShare>
 __global__ __launch_bounds__(64 * kWaves, 4) void compact_kernel(CompactArgs a, int64_t n_wg) {
   __shared__ alignas(16) uint8_t region_sh[kWaves][kRegion + 4];  // + a word that alignbyte may read past the end
   __shared__ uint8_t list_sh[kWaves][kWindow];
@@ -224,12 +226,13 @@ __global__ __launch_bounds__(64 * kWaves, 4) void compact_kernel(CompactArgs a, 
   // publishes its size without waiting for any other
   if (tid == 0) seg_sh = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(a.seg_off + a.n_seg), 1ull);
   lds_barrier();
-  const int64_t b = seg_sh;  // this workgroup's place: segments kWaves b on, or segment b
+  const int64_t b = seg_sh;  // this workgroup's place: segments kWaves / kShare b on
   uint8_t* region = region_sh[w];
-  const int64_t g = kOwn ? b * kWaves + w : b;
+  const int64_t g = b * (kWaves / kShare) + w / kShare;
   const int64_t row = g * a.n_cells;
-  const int per = kOwn ? a.n_cells : ((a.n_cells + kWaves - 1) / kWaves + 63) / 64 * 64;
-  const int c0 = kOwn ? (g < a.n_seg ? 0 : a.n_cells) : (int)((int64_t)per * w < a.n_cells ? (int64_t)per * w : a.n_cells);
+  const int per = kShare == 1 ? a.n_cells : ((a.n_cells + kShare - 1) / kShare + 15) / 16 * 16;
+  const int64_t first = (int64_t)per * (w % kShare);
+  const int c0 = g < a.n_seg && first < a.n_cells ? (int)first : a.n_cells;
   const int c1 = (int)((int64_t)c0 + per < a.n_cells ? (int64_t)c0 + per : a.n_cells);
   uint64_t bytes = 0;
   uint32_t staged = 0;
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void compact_kernel(CompactArgs a, 
       }
       lds_barrier();
       pos = pos_sh + (int64_t)before;
-      if (lane == 0 && g < a.n_seg && (kOwn || w == 0)) a.seg_off[g] = pos;
+      if (lane == 0 && g < a.n_seg && w % kShare == 0) a.seg_off[g] = pos;
     }
     if (staged == 0 || pos >= a.cap) break;
     copy_out(a, region, staged, pos);
@@ -297,16 +300,24 @@ hipError_t launch_compact(const CompactLaunch& l, hipStream_t st) {
   hipLaunchKernelGGL(compact_clear, dim3((unsigned)(((int64_t)l.n_seg + 255) / 256 + (l.n_seg == 0 ? 1 : 0))), dim3(256), 0,
                      st, a);
   hipError_t e = hipGetLastError();
-  // A segment of more than 512 cells takes a workgroup of four or eight
-  // wavefronts; smaller ones a wavefront each, which also keeps the chain of
-  // places short (10,000 segments of 60 cells: 174 us with a workgroup each).
-  const bool own = l.n_cells <= 512;
-  const int64_t n_wg = own ? ((int64_t)l.n_seg + 7) / 8 : l.n_seg;
+  // Wavefronts to a segment: each takes about 64 cells one after another (0.1
+  // us each), up to a workgroup's eight; fewer where the chain of places (about
+  // 20 ns per workgroup) would then be the longer one, while a wavefront's
+  // cells stay near what its region holds. With 1 / 2 / 4 / 8 of them, in us:
+  // 100 segments of 512 cells 81 / 40 / 23 / 17, 1,024 of 128 cells 26 / 20 /
+  // 24 / 38, 2,048 of 512 cells 97 / 73 / 82 / 96, 16,384 of 64 cells 97 / 139 /
+  // 227 / 403.
+  int share = 1;
+  while (share < kWaves && share * 64 < l.n_cells) share *= 2;
+  while (share > 1 && (int64_t)l.n_seg * share / kWaves > 6 * (int64_t)(l.n_cells / share) && l.n_cells / share * 2 <= 300)
+    share /= 2;
+  const int64_t n_wg = ((int64_t)l.n_seg * share + kWaves - 1) / kWaves;
   for (int64_t s = 0; s < n_wg && e == hipSuccess; s += kMaxGrid) {
-    const dim3 n((unsigned)(n_wg - s < kMaxGrid ? n_wg - s : kMaxGrid));
-    if (own) hipLaunchKernelGGL((compact_kernel<8, true>), n, dim3(512), 0, st, a, n_wg);
-    else if (l.n_cells <= 1024) hipLaunchKernelGGL((compact_kernel<4, false>), n, dim3(256), 0, st, a, n_wg);
-    else hipLaunchKernelGGL((compact_kernel<8, false>), n, dim3(512), 0, st, a, n_wg);
+    const dim3 n((unsigned)(n_wg - s < kMaxGrid ? n_wg - s : kMaxGrid)), t(64 * kWaves);
+    if (share == 1) hipLaunchKernelGGL(compact_kernel<1>, n, t, 0, st, a, n_wg);
+    else if (share == 2) hipLaunchKernelGGL(compact_kernel<2>, n, t, 0, st, a, n_wg);
+    else if (share == 4) hipLaunchKernelGGL(compact_kernel<4>, n, t, 0, st, a, n_wg);
+    else hipLaunchKernelGGL(compact_kernel<8>, n, t, 0, st, a, n_wg);
     e = hipGetLastError();
   }
   return e;

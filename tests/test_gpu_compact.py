@@ -188,3 +188,12 @@ def test_compact_full_size(name):
     raw = 24 * c.events_per_seg
     print(f"[gpu-case] {name}: {goff[-1] / G:.0f} B per rank-step vs {raw} B raw ({raw * G / goff[-1]:.0f}x)",
           flush=True)
+
+
+@pytest.mark.parametrize("G,C,fill", [(1030, 100, 0.8), (2050, 130, 0.6), (1100, 129, 0.9), (2100, 300, 0.5),
+                                      (600, 400, 0.9), (1030, 513, 0.3), (4100, 70, 0.7), (33, 129, 1.0)])
+def test_compact_segments_shared_by_wavefronts(G, C, fill):
+    """Segment counts at which one, two, four and eight wavefronts share a
+    segment, with shares that don't divide the cells and a last workgroup that
+    is not full."""
+    test_compact_cell_counts_and_full_records(G, C, fill, 6)
