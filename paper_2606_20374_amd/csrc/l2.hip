@@ -17,6 +17,8 @@
 //               are decided in double where that settles them and by exact
 //               256-bit comparisons where it does not, the reported mean / std
 //               / CV / z are one double operation each.
+//   l2_each     instead, for up to kSmall ranks: a wavefront for every group
+//               and 64 event ids.
 // What bounds l2_stats: the latency of the scattered cell reads and writes (a
 // wavefront's 64 events of one dimension span up to 430 event ids) and the
 // double-precision divisions; 252 MB of cells are read once from HBM and up to
@@ -112,12 +114,13 @@ __global__ __launch_bounds__(256) void l2_owner(L2Args a) {
 
 // ----------------------------------------------------------------- stats
 constexpr int kTile = 2048;  // event ids whose events of one dimension are listed together
-constexpr int kSplit = 16;   // workgroups that share a tile's list, 64 events at a time
+constexpr int kSplit = 16;   // workgroups at most that share a tile's list, 64 events at a time
 constexpr int kWaves = 8;    // wavefronts per workgroup: one small group each, or a share of a large one
-constexpr int kSlots = 4;    // workgroups that share the large ones of kWaves groups
+constexpr int kSlots = 4;    // workgroups at most that share the large ones of kWaves groups
 constexpr int kKeep = 24;    // members of a wavefront whose means stay in LDS between the two passes
 constexpr int kSmall = 32;   // listed members up to which a group is small (one wavefront)
 constexpr int kBatch = 8;    // members whose cells are loaded together
+constexpr int kFew = 2;      // the same in l2_each: 8 take 92 registers and five wavefronts per SIMD, 2 take 68 and seven
 constexpr double kBand = 1e-12;  // of the double comparisons below (their error is below 1e-14)
 constexpr uint32_t kNoMean = 0xFFFFFFFFu;  // no mean that is kept: those lie below it
 
@@ -151,25 +154,27 @@ struct Part {
     return __ballot(ok);
   }
 
-  // Up to kBatch members from todo: their cells of this lane's event, every
+  // Up to B members from todo: their cells of this lane's event, every
   // load issued before the first is used. cnt = 0: no such member or an
   // absent cell.
-  __device__ __forceinline__ void load(const L2Args& a, uint64_t& todo, int32_t m, uint32_t (&row)[kBatch],
-                                       uint32_t (&cnt)[kBatch], int64_t (&sm)[kBatch]) const {
+  template <int B>
+  __device__ __forceinline__ void load(const L2Args& a, uint64_t& todo, int32_t m, uint32_t (&row)[B],
+                                       uint32_t (&cnt)[B], int64_t (&sm)[B]) const {
     const int nb = __popcll(todo);
-    int l = 0;
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      // past the last member the last one is read again and not used
-      if (todo) l = __builtin_ctzll(todo);
+    for (int u = 0; u < B; ++u) {
+      if (u >= nb) {
+        row[u] = 0;
+        cnt[u] = 0;
+        sm[u] = 0;
+        continue;
+      }
+      const int l = __builtin_ctzll(todo);
       todo &= todo - 1;
       row[u] = (uint32_t)__builtin_amdgcn_readlane(m, l) * (uint32_t)a.S + (uint32_t)s;
       cnt[u] = (a.count + (uint64_t)row[u] * (uint32_t)a.E)[(uint32_t)e];
       sm[u] = (a.sum + (uint64_t)row[u] * (uint32_t)a.E)[(uint32_t)e];
     }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      if (u >= nb) cnt[u] = 0;
   }
 };
 
@@ -180,8 +185,9 @@ struct Sums {
 };
 
 // Exact sums over a part's present members; their means go to keep (a row of
-// 64 lanes per member, every 64 listings' rows from a multiple of kBatch on)
+// 64 lanes per member, every 64 listings' rows from a multiple of B on)
 // while they fit. Returns whether keep holds all of them.
+template <int B>
 __device__ __forceinline__ bool sum_part(const L2Args& a, const Part& p, Sums& t, uint32_t (*keep)[64], bool& dom) {
   const int lane = threadIdx.x & 63;
   t = Sums{0, 0, 0};
@@ -191,17 +197,17 @@ __device__ __forceinline__ bool sum_part(const L2Args& a, const Part& p, Sums& t
     int32_t m;
     uint64_t todo = p.at(a, i0, m);
     while (todo) {
-      uint32_t row[kBatch], cnt[kBatch];
-      int64_t sm[kBatch];
+      uint32_t row[B], cnt[B];
+      int64_t sm[B];
       p.load(a, todo, m, row, cnt, sm);
       // means below kNoMean of sums below 2^53: both operands are exact
       // doubles, so the floor of the rounded quotient is exact or one above,
       // and the squares fit 64 bits
       Sums q = t;
       bool wide = false;
-      const bool room = at + kBatch <= kKeep;
+      const bool room = at + B <= kKeep;
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
+      for (int u = 0; u < B; ++u) {
         const double nd = (double)cnt[u], sd = (double)(uint64_t)sm[u], qd = sd / nd;
         wide = wide || (cnt[u] != 0 && !(sd < 0x1p53 && qd < (double)kNoMean));
         uint32_t x = (uint32_t)qd;
@@ -218,7 +224,7 @@ __device__ __forceinline__ bool sum_part(const L2Args& a, const Part& p, Sums& t
       } else {
         kept = false;
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
+        for (int u = 0; u < B; ++u) {
           if (cnt[u] == 0) continue;
           const int64_t x = mean_of(cnt[u], (uint64_t)sm[u]);
           if (x < 0) {
@@ -230,7 +236,7 @@ __device__ __forceinline__ bool sum_part(const L2Args& a, const Part& p, Sums& t
           t.Q += (u128)(uint64_t)x * (uint64_t)x;
         }
       }
-      at += kBatch;
+      at += B;
     }
   }
   return kept;
@@ -316,6 +322,7 @@ struct Group {
 
 // Second pass over a part: z and flags of its members (on: this lane's event
 // is evaluated). Returns the number of stragglers.
+template <int B>
 __device__ __forceinline__ uint32_t write_part(const L2Args& a, const Part& p, const Group& g, bool on, bool kept,
                                                uint32_t (*keep)[64]) {
   const int lane = threadIdx.x & 63;
@@ -331,14 +338,14 @@ __device__ __forceinline__ uint32_t write_part(const L2Args& a, const Part& p, c
         const uint32_t x = keep[at++][lane];
         if (on && x != kNoMean) ns += g.write(a, row, p.e, (double)x, x);
       }
-      at = (at + kBatch - 1) / kBatch * kBatch;
+      at = (at + B - 1) / B * B;
     }
     while (todo) {
-      uint32_t row[kBatch], cnt[kBatch];
-      int64_t sm[kBatch];
+      uint32_t row[B], cnt[B];
+      int64_t sm[B];
       p.load(a, todo, m, row, cnt, sm);
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
+      for (int u = 0; u < B; ++u) {
         if (!on || cnt[u] == 0) continue;
         const int64_t x = mean_of(cnt[u], (uint64_t)sm[u]);
         if (x >= 0) ns += g.write(a, row[u], p.e, (double)x, (uint64_t)x);
@@ -369,7 +376,7 @@ struct LargePart {
 // dimension ran fastest, and the dispatcher's round over XCDs and shader
 // engines would then load a few of them only; x has an odd extent for the
 // same reason.
-__global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t tiles, int32_t n_span) {
+__global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t tiles, int32_t split, int32_t n_span, int32_t slots) {
   __shared__ uint32_t keep_sh[kWaves][kKeep][64];
   __shared__ uint16_t ev[kTile];  // event ids from e0 on
   __shared__ int32_t wave_n[kWaves];
@@ -383,6 +390,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = (int)(blockIdx.z / (uint32_t)a.n_dims), d = (int)(blockIdx.z % (uint32_t)a.n_dims);
   const int slot = (int)blockIdx.y / n_span, g0 = (int)blockIdx.y % n_span * kWaves;
+  if (slot >= slots) return;
   // bit j: group g0 + j is a small / a large one of the dimension
   int32_t lo = 0, hi = 0;
   if (lane < kWaves && g0 + lane < a.max_groups) {
@@ -392,10 +400,10 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
   }
   const bool ok = lo >= 0 && hi > lo && hi <= a.R;
   const uint32_t some = (uint32_t)__ballot(ok && hi - lo <= kSmall && slot == 0);
-  const uint32_t many = (uint32_t)__ballot(ok && hi - lo > kSmall && lane % kSlots == slot);
+  const uint32_t many = (uint32_t)__ballot(ok && hi - lo > kSmall && lane % slots == slot);
   if ((some | many) == 0) return;
   bool dom = false;
-  const uint32_t items = (uint32_t)tiles * kSplit;
+  const uint32_t items = (uint32_t)tiles * (uint32_t)split;
   for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
     const int64_t e0 = (int64_t)(it % (uint32_t)tiles) * kTile;
     const int c0 = (int)(it / (uint32_t)tiles) * 64;
@@ -427,7 +435,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
       }
     }
     lds_barrier();
-    for (int c = c0; c < M; c += 64 * kSplit) {
+    for (int c = c0; c < M; c += 64 * split) {
       const bool on = c + lane < M;
       Part p{a.mem + (int64_t)d * a.R, a.owner + (int64_t)d * a.R, 0, 0, 0, s, (int)e0 + ev[on ? c + lane : c]};
       // first the small groups together, then the large ones in turn
@@ -445,7 +453,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
           p.hi = (int32_t)(first + len * (w + 1) / kWaves);
         }
         Sums t{0, 0, 0};
-        const bool kept = busy && sum_part(a, p, t, keep_sh[w], dom);
+        const bool kept = busy && sum_part<kBatch>(a, p, t, keep_sh[w], dom);
         if (large) {
           sh.large.n[w][lane] = t.n;
           sh.large.S[w][lane] = t.S;
@@ -464,7 +472,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
         if (busy) {
           Group gr;
           gr.set(a, t);
-          const uint32_t ns = write_part(a, p, gr, on && gr.eval, kept, keep_sh[w]);
+          const uint32_t ns = write_part<kBatch>(a, p, gr, on && gr.eval, kept, keep_sh[w]);
           if (large) {
             if (ns) atomicAdd(&ns_sh[lane], ns);
             lds_barrier();
@@ -512,6 +520,41 @@ __global__ __launch_bounds__(64 * kWaves, 4) void l2_stats(L2Args a, int32_t til
   if (__ballot(dom) != 0 && lane == 0) raise(a.o.dev_status, ARGUS_DEV_L2_DOMAIN);
 }
 
+// A wavefront for every group and 64 event ids of a step and dimension, for
+// so few ranks that no group is large. Its lanes are idle where an event has
+// another dimension, but seven such wavefronts share a SIMD against four of
+// l2_stats, and none waits for another: 16 ranks x 1,000 steps x 50 events 70 us
+// with l2_stats, 52 us so; 32 x 200 x 200 103 and 67 us; 8 x 2,000 x 50 97 and
+// 31 us.
+__global__ __launch_bounds__(64) void l2_each(L2Args a) {
+  __shared__ uint32_t keep[kKeep][64];
+  const int lane = threadIdx.x, g = blockIdx.y;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int s = (int)(blockIdx.z / (uint32_t)a.n_dims), d = (int)(blockIdx.z % (uint32_t)a.n_dims);
+  const int32_t* off = a.off + (int64_t)d * (a.max_groups + 1) + g;
+  const int32_t lo = off[0], hi = off[1];
+  const bool mine = e < a.E && a.route[e] == d;
+  if (__ballot(mine) == 0 || lo < 0 || hi <= lo || hi > a.R) return;
+  const Part p{a.mem + (int64_t)d * a.R, a.owner + (int64_t)d * a.R, (uint32_t)g * (uint32_t)a.R, lo, hi, s,
+               (int)(e < a.E ? e : a.E - 1)};
+  bool dom = false;
+  Sums t;
+  const bool kept = sum_part<kFew>(a, p, t, keep, dom);
+  if (__ballot(dom && mine) != 0 && lane == 0) raise(a.o.dev_status, ARGUS_DEV_L2_DOMAIN);
+  Group gr;
+  gr.set(a, t);
+  uint32_t ns = 0;
+  if (__ballot(mine && gr.eval) != 0) ns = write_part<kFew>(a, p, gr, mine && gr.eval, kept, keep);
+  if (!mine) return;
+  const int64_t go = ((int64_t)s * a.E + e) * a.max_groups + g;
+  a.o.n[go] = t.n;
+  a.o.n_strag[go] = ns;
+  a.o.mean_ns[go] = gr.mean;
+  a.o.std_ns[go] = gr.sd;
+  a.o.cv[go] = gr.cv;
+  a.o.cls[go] = gr.cls;
+}
+
 }  // namespace
 
 size_t l2_workspace_bytes(int32_t R, int32_t n_dims) {
@@ -534,11 +577,32 @@ hipError_t launch_l2(const L2Launch& l, hipStream_t st) {
   hipLaunchKernelGGL(l2_owner, dim3(l.g.max_groups, l.g.n_dims), dim3(256), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t tiles = ((int64_t)l.E + kTile - 1) / kTile, items = tiles * kSplit;
+  const unsigned z = (unsigned)((int64_t)l.S * l.g.n_dims);
+  if (l.R <= kSmall) {
+    hipLaunchKernelGGL(l2_each, dim3((unsigned)(((int64_t)l.E + 63) / 64), l.g.max_groups, z), dim3(64), 0, st, a);
+    return hipGetLastError();
+  }
+  // A workgroup that finds nothing to do costs 2.5 ns: no more shares of a tile
+  // than it has 64 events, no more slots than the ranks make large groups, and
+  // fewer shares where the grid is large and the steps keep the chip busy
+  // without them (300 ranks x 60 steps x 1,000 events: 902 us with 16 shares,
+  // 466 us with one; 64 x 200 x 130: 1,077 and 94 us with 16 shares x 4 slots
+  // and without; 10,240 x 1 x 2,048: 382, 375 with 8, 436 with 4). The extents
+  // are odd so that workgroups with work do not fall on a few shader engines
+  // only (256 x 100 x 64, slot 0 of four at work: 252 us with 32 along y, 79
+  // with 33).
+  const int64_t tiles = ((int64_t)l.E + kTile - 1) / kTile;
   const int32_t groups = (l.g.max_groups + kWaves - 1) / kWaves;
-  hipLaunchKernelGGL(l2_stats, dim3((unsigned)(items < (1 << 20) ? items | 1 : (1 << 20) | 1), groups * kSlots,
-                                    (unsigned)((int64_t)l.S * l.g.n_dims)),
-                     dim3(64 * kWaves), 0, st, a, (int32_t)tiles, groups);
+  int32_t split = l.E < 64 * kSplit ? (l.E + 63) / 64 : kSplit;
+  const int32_t large = l.R / (kSmall + 1), slots = large < kSlots ? large : kSlots;
+  const unsigned y = (unsigned)(groups * slots) | 1u;
+  unsigned x;
+  for (;; split /= 2) {
+    const int64_t items = tiles * split;
+    x = (unsigned)(items < (1 << 20) ? items | 1 : (1 << 20) | 1);
+    if (split == 1 || (int64_t)l.S * items * slots <= 64 || (int64_t)x * y * z <= 20000) break;
+  }
+  hipLaunchKernelGGL(l2_stats, dim3(x, y, z), dim3(64 * kWaves), 0, st, a, (int32_t)tiles, split, groups, slots);
   return hipGetLastError();
 }
 

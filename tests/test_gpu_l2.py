@@ -215,3 +215,27 @@ def test_l2_mixed_sizes_one_dimension(E):
     sm = rng.integers(10**5, 10**6, size=R * S * E) * cnt.astype(np.int64)
     _both(cnt, sm, R, S, E, np.zeros(E, np.uint8), off, rng.permutation(R).astype(np.int32).reshape(1, R),
           f"mixed sizes, E {E}", z_pm=1500)
+
+
+@pytest.mark.parametrize("R,S,E", [(8, 3, 64), (31, 2, 65), (32, 5, 130), (32, 1, 2049), (33, 5, 130), (40, 2, 1),
+                                   (70, 200, 700), (150, 130, 100)])
+def test_l2_few_ranks_and_many_steps(R, S, E):
+    """Rank counts around the one (32) up to which every group has wavefronts
+    of its own, and steps and events at which a workgroup takes several
+    shares of a tile in turn; mixed group sizes with second and invalid
+    listings, absent cells, unrouted events and means out of the domain."""
+    _announce(f"l2 R={R} S={S} E={E}")
+    rng = np.random.default_rng(R * 1009 + S * 31 + E)
+    cnt = rng.integers(0, 4, size=R * S * E).astype(np.uint32)
+    xs = rng.integers(10**5, 10**6, size=R * S * E)
+    xs[rng.integers(0, R * S * E, size=3)] = 2**40 + 5
+    D, G = 3, max(2, R // 5)
+    off, mem = np.zeros((D, G + 1), np.int32), np.zeros((D, R), np.int32)
+    for d in range(D):
+        off[d, 1:G] = np.sort(rng.integers(0, R + 1, size=G - 1)) if d else np.minimum(np.arange(1, G), R)
+        off[d, G] = R
+        mem[d] = rng.permutation(R)
+    mem[1, R // 2] = mem[1, 0]
+    mem[2, 0] = -1
+    route = rng.choice([0, 1, 1, 2, 0xFF], size=E).astype(np.uint8)
+    _both(cnt, xs * cnt.astype(np.int64), R, S, E, route, off, mem, f"few ranks {R}x{S}x{E}", z_pm=1500)
