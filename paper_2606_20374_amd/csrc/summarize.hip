@@ -15,10 +15,10 @@
 //   WIN-bin window of the octave histogram (a lognormal mode spans two or
 //   three octaves, a kernel whose positions run at 1x, 3x and 9x five or
 //   six). In the dense layout the window has ten bins around the first
-//   duration seen; where the map or table leaves room for six only, bin b is
-//   counted at b mod 6 while the bins seen span at most six octaves, wherever
-//   the first lay. Bins outside the window go to a small pool of full 32-bin
-//   records that a kernel claims on first need.
+//   duration seen; where the map or table leaves room for fewer, eight or six,
+//   bin b is counted at b mod 8 or 6 while the bins seen span at most so many
+//   octaves, wherever the first lay. Bins outside the window go to a small
+//   pool of full 32-bin records that a kernel claims on first need.
 // * Keys (kernel ids, or (kernel id, stream) pairs as id * n_streams +
 //   stream: section 5.2 groups per kernel and stream) map to LDS slots
 //   directly when the key space fits (dense), through an LDS key->slot map
@@ -46,7 +46,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef long long v2l __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 1024;
-constexpr int kPool = 32;  // full 32-bin records per pass
 constexpr uint32_t kSpanMask = 0x3E00FFu;
 constexpr uint32_t kSpanUnset = 0xFFu;  // first bin of a span: none seen yet
 constexpr uint32_t kStNone = 0, kStBusy = 0xFE, kStPoison = 0xFF;
@@ -63,9 +62,9 @@ constexpr int kDense = 0, kMapped = 1, kHashed = 2;
 constexpr uint32_t kMapEmpty = 0xFFFF, kMapBusy = 0xFFFE, kMapDefer = 0xFFFD, kMapDone = 0xFFFC;
 
 // meta word of a slot: bits 0-7 first bin of the window's span (0xFF unset),
-// bits 17-21 its last bin (not kept in dense mode: first + WIN - 1), bits 8-15 full-record state (0 none, 1..kPool
-// record index + 1, 0xFE being claimed, 0xFF pool exhausted: redo in another
-// pass), bit 16 already written.
+// bits 17-21 its width, last bin - first (not kept in dense mode: WIN - 1),
+// bits 8-15 full-record state (0 none, 1..kPool record index + 1, 0xFE being
+// claimed, 0xFF pool exhausted: redo in another pass), bit 16 already written.
 //
 // map entry (mapped mode, 16 bits, two per 32-bit word): a slot index, or
 // empty / being claimed / deferred to another pass / already written.
@@ -77,6 +76,8 @@ struct Smem {
   long long mm[NSLOT][2];  // min, max (one 16-byte read per event)
   uint32_t win[NSLOT][WIN];
   uint32_t meta[NSLOT];
+  // full 32-bin records of a pass: in mapped mode as many as the LDS has room for
+  static constexpr int kPool = MODE == kMapped ? 27 : 32;
   uint32_t pool[kPool][NB];
   unsigned long long stream_busy[ARGUS_MAX_STREAMS];
   alignas(16) uint32_t map[MODE == kMapped ? kMapIds / 2 : MODE == kHashed ? kHash : 1];
@@ -213,7 +214,7 @@ struct Seg {
           if (old == m) {
             const uint32_t idx = atomicAdd(&sm.npool, 1u);
             uint32_t fin;
-            if (idx < (uint32_t)kPool) {
+            if (idx < (uint32_t)S::kPool) {
               atomicAdd(&sm.pool[idx][b], 1u);
               fin = (m & ~0xFF00u) | ((idx + 1u) << 8);
             } else {
@@ -237,28 +238,29 @@ struct Seg {
   // mmv: min and max of the slot as read before this event (possibly stale:
   // min only falls and max only rises, so a stale read can only cause an
   // extra atomic, never a missed one)
-  // Span of the window in meta word m (its first bin set), first and last
-  // bin, and the place of bin b of the span in the window.
+  // Span of the window in meta word m (its first bin set): first bin, width
+  // (last bin - first), and the place of bin b of the span in the window.
   __device__ __forceinline__ static int span_lo(uint32_t m) { return (int)(m & 0xFFu); }
-  __device__ __forceinline__ static int span_hi(uint32_t m) {
-    return MODE == kDense ? span_lo(m) + WIN - 1 : (int)((m >> 17) & 31u);
+  __device__ __forceinline__ static uint32_t span_width(uint32_t m) {
+    return MODE == kDense ? (uint32_t)WIN - 1 : (m >> 17) & 31u;
   }
   __device__ __forceinline__ static int win_at(uint32_t m, int b) {
-    static_assert(MODE == kDense || WIN == 6, "b * 43 >> 8 is b / 6 up to 31");
-    return MODE == kDense ? b - span_lo(m) : b - WIN * ((b * 43) >> 8);
+    static_assert(MODE == kDense || WIN == 6 || WIN == 8, "b * 43 >> 8 is b / 6 up to 31");
+    return MODE == kDense ? b - span_lo(m) : WIN == 8 ? b & 7 : b - WIN * ((b * 43) >> 8);
   }
 
-  // Mapped and hashed modes: widen the span of slot's window to hold bin b (m: its meta word, updated
-  // to the newest read); false when that would pass WIN octaves. Spans only
+  // Mapped and hashed modes: widen the span of slot's window to hold bin b
+  // (m: its meta word, updated to the newest read); false when that would pass
+  // WIN octaves. Spans only
   // widen and a state changes at most twice, and a failed swap means that
   // another lane's succeeded, so the loop ends after a bounded count.
   __device__ bool span_widen(int slot, uint32_t& m, int b) {
     while (true) {
       const bool unset = (m & 0xFFu) == kSpanUnset;
       const int lo = unset || b < span_lo(m) ? b : span_lo(m);
-      const int hi = unset || b > span_hi(m) ? b : span_hi(m);
+      const int last = span_lo(m) + (int)span_width(m), hi = unset || b > last ? b : last;
       if (hi - lo >= WIN) return false;
-      const uint32_t want = (m & ~kSpanMask) | (uint32_t)lo | ((uint32_t)hi << 17);
+      const uint32_t want = (m & ~kSpanMask) | (uint32_t)lo | ((uint32_t)(hi - lo) << 17);
       if (want == m) return true;
       const uint32_t old = atomicCAS(&sm.meta[slot], m, want);
       if (old == m) {
@@ -283,8 +285,8 @@ struct Seg {
       }
       in = (unsigned)(b - span_lo(m)) < (unsigned)WIN;
     } else {
-      // unset: the first bin reads as 255, so no bin lies in the span
-      in = (b >= span_lo(m) && b <= span_hi(m)) || span_widen(slot, m, b);
+      // unset: the first bin reads as 255 and the width as 0, so no bin lies in the span
+      in = (uint32_t)(b - span_lo(m)) <= span_width(m) || span_widen(slot, m, b);
     }
     if (in)
       atomicAdd(&sm.win[slot][win_at(m, b)], 1u);
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
         for (int i = tid; i < kHash; i += kThreads) sm.map[i] = kHashEmpty;
       if (MODE != kDense)
         for (int s = tid; s < NSLOT; s += kThreads) sg.slot_reset(s);
-      for (int i = tid; i < kPool * NB; i += kThreads) (&sm.pool[0][0])[i] = 0;
+      for (int i = tid; i < sm.kPool * NB; i += kThreads) (&sm.pool[0][0])[i] = 0;
       if (tid == 0) {
         sm.npool = 0;
         sm.poison = 0;
@@ -583,7 +585,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int b = 4 * q + j;
-          v[j] = b >= sg.span_lo(m) && b <= sg.span_hi(m) ? sm.win[s][sg.win_at(m, b)] : 0u;
+          v[j] = (uint32_t)(b - sg.span_lo(m)) <= sg.span_width(m) ? sm.win[s][sg.win_at(m, b)] : 0u;
           if (pst != kStNone) v[j] += sm.pool[pst - 1][b];
         }
         const int64_t c = g * K + kb + (MODE != kDense ? (int)sm.slot_kid[s] : s);
@@ -700,10 +702,14 @@ hipError_t launch_summarize(const SummarizeLaunch& l, hipStream_t st) {
   // more read (512 segments of 400,000 events, 32,768 keys of which about
   // 1,900 occur, a third of them at 1x, 3x and 9x: 3.6 ms by ranges, 3.2 with
   // the table, 1.12 with the table and spans; the events read once take 0.8).
-  // Up to 16,384 keys the map's one two-byte read is the cheaper lookup; a
-  // key space that fits the slots needs neither, and its ten-bin window loses
-  // 4% to the span's extra instructions (2,048 keys: 3.55 against 3.66 ms).
-  if (n_keys <= kMapIds) return launch_t<2048, 6, kMapped>(a, l.n_seg, st);
+  // Up to 16,384 keys the map's one two-byte read is the cheaper lookup, with
+  // room for windows of eight octaves: 4,096 segments of 200,000 events over
+  // 8,200 ids, few of them wide, 4.38 ms (4.45 with six bins around the first
+  // duration), 512 of 400,000 over 4,000 (kernel, stream) keys at up to three
+  // scales 0.93 (2.11). A key space that fits the slots needs neither, and its
+  // ten-bin window loses 4% to the span's extra instructions (2,048 keys: 3.55
+  // against 3.66 ms).
+  if (n_keys <= kMapIds) return launch_t<2048, 8, kMapped>(a, l.n_seg, st);
   return launch_t<2048, 6, kHashed>(a, l.n_seg, st);
 }
 

@@ -451,3 +451,26 @@ def test_sparse_ids_in_runs(K):
     torch.cuda.synchronize()
     o = oracle.summarize(ev, K, 5)
     P.assert_int_equal(g, o, P.SUM_INT_FIELDS, f"runs K={K}")
+
+
+@pytest.mark.parametrize("K", [300, 6000, 20_000])
+def test_window_spans(K):
+    """Kernels whose durations fill 1 to 11 octaves from every octave on, in
+    random order: spans that fit the histogram window of the dense, mapped and
+    hashed id spaces wherever it wraps, that end at its last octave and that
+    pass it by one, more of these than there are full records."""
+    _announce(f"window spans K={K}")
+    rng = np.random.default_rng(K)
+    ids = np.sort(rng.choice(K, 300, replace=False))
+    n = 30_000
+    pick = rng.integers(0, 300, n)
+    lo, width = pick % 32, 1 + (pick // 32 + pick) % 11
+    b = np.minimum(lo + rng.integers(0, width), 33)
+    ev = _random_events(n, K, 5, seed=K, seg_lengths=[n - 7, 7])
+    ev["kernel_id"], ev["stream"] = ids[pick].astype(np.int32), (pick % 5).astype(np.int32)
+    ev["start_ns"] = np.full(n, 2**60, np.int64)
+    ev["end_ns"] = ev["start_ns"] + np.where(b == 0, rng.integers(0, 2, n), 2**b + rng.integers(0, 2**b))
+    g = pa.summarize(_dev_events(ev), 2, 1, K, 5)
+    torch.cuda.synchronize()
+    o = oracle.summarize(ev, K, 5)
+    P.assert_int_equal(g, o, P.SUM_INT_FIELDS, f"spans K={K}")
