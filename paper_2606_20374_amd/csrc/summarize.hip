@@ -51,8 +51,8 @@ constexpr uint32_t kSpanUnset = 0xFFu;  // first bin of a span: none seen yet
 constexpr uint32_t kStNone = 0, kStBusy = 0xFE, kStPoison = 0xFF;
 constexpr uint32_t kDone = 1u << 16;
 constexpr int kMapIds = 16384;  // ids in mapped mode
-// Bound on the iterations of one claim wait, and on the passes over one key
-// range that may end with a wait cut short. A claim's owner publishes after
+// Bound on the iterations of one claim wait, and on the passes over one segment
+// that may end with a wait cut short. A claim's owner publishes after
 // a fixed number of its own instructions, so no wait comes near the bound
 // unless the code around it is compiled wrongly; the bounds make the kernel
 // exit (and report) in that case instead of hanging.
@@ -312,7 +312,7 @@ struct Seg {
 template <int NSLOT, int WIN, int MODE>
 __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& a, const int32_t (&kid)[4],
                                          const int32_t (&st)[4], const int64_t (&t0)[4], const int64_t (&t1)[4],
-                                         int n, bool first_scan, int kb, int nk, uint32_t& nv, uint32_t& ni,
+                                         int n, bool first_scan, uint32_t& nv, uint32_t& ni,
                                          unsigned long long& busy, long long& tf, long long& tl) {
   uint64_t d[4];
   int lk[4];
@@ -333,7 +333,7 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& 
       }
     }
     const uint32_t key = a.key_ns ? (uint32_t)kid[j] * (uint32_t)a.key_ns + (uint32_t)st[j] : (uint32_t)kid[j];
-    lk[j] = valid && key - (uint32_t)kb < (uint32_t)nk ? (int)(key - (uint32_t)kb) : -1;
+    lk[j] = valid ? (int)key : -1;
   }
   // per-kernel updates two events at a time: their LDS lookups are issued
   // together, and the live register set stays small enough that nothing
@@ -435,194 +435,189 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
   long long tf = INT64_MAX, tl = INT64_MIN;
   bool first_scan = true;
   int n_stuck = 0;  // passes of this segment that ended with a wait cut short
-  constexpr int kRange = MODE == kHashed ? kHashIds : MODE == kMapped ? kMapIds : NSLOT;
 
-  for (int32_t kb = 0; kb < K; kb += kRange) {
-    const int nk = K - kb < kRange ? K - kb : kRange;
+  if (MODE == kHashed)
+    for (int i = tid; i < kHashIds / 32; i += kThreads) sm.done[i] = 0;
+  else if (MODE == kMapped)
+    for (int i = tid; i < kMapIds / 2; i += kThreads) sm.map[i] = 0xFFFFFFFFu;
+  else
+    for (int s = tid; s < K; s += kThreads) sg.slot_reset(s);
+  while (true) {
+    // the mapped and hashed modes hand out slots afresh in every pass
     if (MODE == kHashed)
-      for (int i = tid; i < kHashIds / 32; i += kThreads) sm.done[i] = 0;
-    else if (MODE == kMapped)
-      for (int i = tid; i < kMapIds / 2; i += kThreads) sm.map[i] = 0xFFFFFFFFu;
-    else
-      for (int s = tid; s < nk; s += kThreads) sg.slot_reset(s);
-    while (true) {
-      // the mapped and hashed modes hand out slots afresh in every pass
-      if (MODE == kHashed)
-        for (int i = tid; i < kHash; i += kThreads) sm.map[i] = kHashEmpty;
-      if (MODE != kDense)
-        for (int s = tid; s < NSLOT; s += kThreads) sg.slot_reset(s);
-      for (int i = tid; i < sm.kPool * NB; i += kThreads) (&sm.pool[0][0])[i] = 0;
-      if (tid == 0) {
-        sm.npool = 0;
-        sm.poison = 0;
-        sm.nslots = 0;
-        sm.stuck = 0;
-      }
-      lds_barrier();
+      for (int i = tid; i < kHash; i += kThreads) sm.map[i] = kHashEmpty;
+    if (MODE != kDense)
+      for (int s = tid; s < NSLOT; s += kThreads) sg.slot_reset(s);
+    for (int i = tid; i < sm.kPool * NB; i += kThreads) (&sm.pool[0][0])[i] = 0;
+    if (tid == 0) {
+      sm.npool = 0;
+      sm.poison = 0;
+      sm.nslots = 0;
+      sm.stuck = 0;
+    }
+    lds_barrier();
 
-      // unaligned head and tail: at most 3 events each, on the first threads
-      if (a.vec_ok) {
+    // unaligned head and tail: at most 3 events each, on the first threads
+    if (a.vec_ok) {
+      int32_t kid[4], st[4];
+      int64_t t0[4], t1[4];
+      int n = 0;
+      const int64_t h = a4 - lo, t = hi - b4;
+      const int64_t i = tid < h ? lo + tid : (tid - h < t ? b4 + (tid - h) : -1);
+      if (i >= 0) {
+        kid[0] = a.kernel_id[i];
+        st[0] = a.stream[i];
+        t0[0] = a.start_ns[i];
+        t1[0] = a.end_ns[i];
+        n = 1;
+      }
+      for (int j = n; j < 4; ++j) {
+        kid[j] = -1;
+        st[j] = 0;
+        t0[j] = t1[j] = 0;
+      }
+      if (n) process4(sg, a, kid, st, t0, t1, n, first_scan, nv, ni, busy, tf, tl);
+    }
+    if (!a.vec_ok) {
+      // scalar fallback for unaligned arrays: four strided events per thread
+      for (int64_t i0 = lo + tid; i0 < hi; i0 += 4ll * kThreads) {
         int32_t kid[4], st[4];
         int64_t t0[4], t1[4];
         int n = 0;
-        const int64_t h = a4 - lo, t = hi - b4;
-        const int64_t i = tid < h ? lo + tid : (tid - h < t ? b4 + (tid - h) : -1);
-        if (i >= 0) {
-          kid[0] = a.kernel_id[i];
-          st[0] = a.stream[i];
-          t0[0] = a.start_ns[i];
-          t1[0] = a.end_ns[i];
-          n = 1;
-        }
-        for (int j = n; j < 4; ++j) {
-          kid[j] = -1;
-          st[j] = 0;
-          t0[j] = t1[j] = 0;
-        }
-        if (n) process4(sg, a, kid, st, t0, t1, n, first_scan, kb, nk, nv, ni, busy, tf, tl);
-      }
-      if (!a.vec_ok) {
-        // scalar fallback for unaligned arrays: four strided events per thread
-        for (int64_t i0 = lo + tid; i0 < hi; i0 += 4ll * kThreads) {
-          int32_t kid[4], st[4];
-          int64_t t0[4], t1[4];
-          int n = 0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int64_t i = i0 + (int64_t)j * kThreads;  // in range for a prefix of j
-            const bool in = i < hi;
-            kid[j] = in ? a.kernel_id[i] : -1;
-            st[j] = in ? a.stream[i] : 0;
-            t0[j] = in ? a.start_ns[i] : 0;
-            t1[j] = in ? a.end_ns[i] : 0;
-            n += in;
-          }
-          process4(sg, a, kid, st, t0, t1, n, first_scan, kb, nk, nv, ni, busy, tf, tl);
-        }
-      }
-      // aligned body: group q holds events 4q..4q+3; the next group's loads
-      // are issued before the current group is processed
-      {
-        int64_t q = qa + tid;
-        v4i nk4 = 0, ns4 = 0;
-        v2l na0 = 0, na1 = 0, nb0 = 0, nb1 = 0;
-        if (q < qb) {
-          nk4 = __builtin_nontemporal_load(K4 + q);
-          ns4 = __builtin_nontemporal_load(S4 + q);
-          na0 = __builtin_nontemporal_load(T0 + 2 * q);
-          na1 = __builtin_nontemporal_load(T0 + 2 * q + 1);
-          nb0 = __builtin_nontemporal_load(T1 + 2 * q);
-          nb1 = __builtin_nontemporal_load(T1 + 2 * q + 1);
-        }
-        while (q < qb) {
-          const int32_t kid[4] = {nk4.x, nk4.y, nk4.z, nk4.w};
-          const int32_t st[4] = {ns4.x, ns4.y, ns4.z, ns4.w};
-          const int64_t t0[4] = {na0.x, na0.y, na1.x, na1.y};
-          const int64_t t1[4] = {nb0.x, nb0.y, nb1.x, nb1.y};
-          const int64_t qn = q + kThreads;
-          if (qn < qb) {
-            nk4 = __builtin_nontemporal_load(K4 + qn);
-            ns4 = __builtin_nontemporal_load(S4 + qn);
-            na0 = __builtin_nontemporal_load(T0 + 2 * qn);
-            na1 = __builtin_nontemporal_load(T0 + 2 * qn + 1);
-            nb0 = __builtin_nontemporal_load(T1 + 2 * qn);
-            nb1 = __builtin_nontemporal_load(T1 + 2 * qn + 1);
-          }
-          process4(sg, a, kid, st, t0, t1, 4, first_scan, kb, nk, nv, ni, busy, tf, tl);
-          q = qn;
-        }
-      }
-      first_scan = false;
-      lds_barrier();
-
-      // A claim wait cut short dropped an update: every kernel of this pass is
-      // redone (the per-segment aggregates were complete in the first scan).
-      // After kMaxStuckPasses such passes the results are flushed as they are
-      // and the condition is reported.
-      const bool stuck = sm.stuck != 0;
-      const bool redo_pass = stuck && n_stuck < kMaxStuckPasses;
-      if (stuck) {
-        if (!redo_pass && tid == 0 && a.dev_status) atomicOr(a.dev_status, (int32_t)ARGUS_DEV_SUMMARY_STALLED);
-        ++n_stuck;
-      }
-
-      // flush: the count of every slot; sum, min, max and wire size of the
-      // present ones
-      const int nslot = MODE != kDense ? (int)(sm.nslots < (uint32_t)NSLOT ? sm.nslots : NSLOT) : nk;
-      for (int s = tid; s < (redo_pass ? 0 : nslot); s += kThreads) {
-        const uint32_t m = sm.meta[s];
-        const uint32_t pst = (m >> 8) & 0xFFu;
-        if ((m & kDone) || pst == kStPoison) continue;
-        uint32_t cnt = 0, nnz = 0;
-#pragma unroll
-        for (int w = 0; w < WIN; ++w) {
-          cnt += sm.win[s][w];
-          nnz += sm.win[s][w] != 0;
-        }
-        if (pst != kStNone) {
-          for (int b = 0; b < NB; ++b) {
-            cnt += sm.pool[pst - 1][b];
-            nnz += sm.pool[pst - 1][b] != 0;
-          }
-        }
-        const int64_t c = g * K + kb + (MODE != kDense ? (int)sm.slot_kid[s] : s);
-        a.count[c] = cnt;
-        if (cnt) {
-          a.sum_ns[c] = (int64_t)sm.sum[s];
-          a.min_ns[c] = sm.mm[s][0];
-          a.max_ns[c] = sm.mm[s][1];
-          wire += 33u + 5u * nnz;
-        }
-      }
-      // flush: histograms of the present slots (their span is set),
-      // four bins per thread, 16-byte stores
-      for (int it = tid; it < (redo_pass ? 0 : nslot) * (NB / 4); it += kThreads) {
-        const int s = it >> 3, q = it & 7;
-        const uint32_t m = sm.meta[s];
-        const uint32_t pst = (m >> 8) & 0xFFu;
-        if ((m & kDone) || pst == kStPoison || (m & 0xFFu) == kSpanUnset) continue;
-        uint32_t v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int b = 4 * q + j;
-          v[j] = (uint32_t)(b - sg.span_lo(m)) <= sg.span_width(m) ? sm.win[s][sg.win_at(m, b)] : 0u;
-          if (pst != kStNone) v[j] += sm.pool[pst - 1][b];
+          const int64_t i = i0 + (int64_t)j * kThreads;  // in range for a prefix of j
+          const bool in = i < hi;
+          kid[j] = in ? a.kernel_id[i] : -1;
+          st[j] = in ? a.stream[i] : 0;
+          t0[j] = in ? a.start_ns[i] : 0;
+          t1[j] = in ? a.end_ns[i] : 0;
+          n += in;
         }
-        const int64_t c = g * K + kb + (MODE != kDense ? (int)sm.slot_kid[s] : s);
-        *reinterpret_cast<uint4*>(a.hist + c * NB + 4 * q) = make_uint4(v[0], v[1], v[2], v[3]);
+        process4(sg, a, kid, st, t0, t1, n, first_scan, nv, ni, busy, tf, tl);
       }
-      lds_barrier();
-      const bool again = sm.poison != 0 || redo_pass;
-      // mark what was written; kernels that ran out of room start over
-      for (int s = tid; s < nslot; s += kThreads) {
-        const uint32_t m = sm.meta[s];
-        if (m & kDone) continue;
-        const bool redo = redo_pass || ((m >> 8) & 0xFFu) == kStPoison;
-        if (MODE == kHashed) {
-          const uint32_t k = sm.slot_kid[s];
-          if (!redo) atomicOr(&sm.done[k >> 5], 1u << (k & 31));
-        } else if (MODE == kMapped) {
-          sg.map_set(sm.slot_kid[s], redo ? (uint16_t)kMapEmpty : (uint16_t)kMapDone);
-        } else if (redo) {
-          sg.slot_reset(s);
-        } else {
-          sm.meta[s] = m | kDone;
+    }
+    // aligned body: group q holds events 4q..4q+3; the next group's loads
+    // are issued before the current group is processed
+    {
+      int64_t q = qa + tid;
+      v4i nk4 = 0, ns4 = 0;
+      v2l na0 = 0, na1 = 0, nb0 = 0, nb1 = 0;
+      if (q < qb) {
+        nk4 = __builtin_nontemporal_load(K4 + q);
+        ns4 = __builtin_nontemporal_load(S4 + q);
+        na0 = __builtin_nontemporal_load(T0 + 2 * q);
+        na1 = __builtin_nontemporal_load(T0 + 2 * q + 1);
+        nb0 = __builtin_nontemporal_load(T1 + 2 * q);
+        nb1 = __builtin_nontemporal_load(T1 + 2 * q + 1);
+      }
+      while (q < qb) {
+        const int32_t kid[4] = {nk4.x, nk4.y, nk4.z, nk4.w};
+        const int32_t st[4] = {ns4.x, ns4.y, ns4.z, ns4.w};
+        const int64_t t0[4] = {na0.x, na0.y, na1.x, na1.y};
+        const int64_t t1[4] = {nb0.x, nb0.y, nb1.x, nb1.y};
+        const int64_t qn = q + kThreads;
+        if (qn < qb) {
+          nk4 = __builtin_nontemporal_load(K4 + qn);
+          ns4 = __builtin_nontemporal_load(S4 + qn);
+          na0 = __builtin_nontemporal_load(T0 + 2 * qn);
+          na1 = __builtin_nontemporal_load(T0 + 2 * qn + 1);
+          nb0 = __builtin_nontemporal_load(T1 + 2 * qn);
+          nb1 = __builtin_nontemporal_load(T1 + 2 * qn + 1);
+        }
+        process4(sg, a, kid, st, t0, t1, 4, first_scan, nv, ni, busy, tf, tl);
+        q = qn;
+      }
+    }
+    first_scan = false;
+    lds_barrier();
+
+    // A claim wait cut short dropped an update: every kernel of this pass is
+    // redone (the per-segment aggregates were complete in the first scan).
+    // After kMaxStuckPasses such passes the results are flushed as they are
+    // and the condition is reported.
+    const bool stuck = sm.stuck != 0;
+    const bool redo_pass = stuck && n_stuck < kMaxStuckPasses;
+    if (stuck) {
+      if (!redo_pass && tid == 0 && a.dev_status) atomicOr(a.dev_status, (int32_t)ARGUS_DEV_SUMMARY_STALLED);
+      ++n_stuck;
+    }
+
+    // flush: the count of every slot; sum, min, max and wire size of the
+    // present ones
+    const int nslot = MODE != kDense ? (int)(sm.nslots < (uint32_t)NSLOT ? sm.nslots : NSLOT) : K;
+    for (int s = tid; s < (redo_pass ? 0 : nslot); s += kThreads) {
+      const uint32_t m = sm.meta[s];
+      const uint32_t pst = (m >> 8) & 0xFFu;
+      if ((m & kDone) || pst == kStPoison) continue;
+      uint32_t cnt = 0, nnz = 0;
+#pragma unroll
+      for (int w = 0; w < WIN; ++w) {
+        cnt += sm.win[s][w];
+        nnz += sm.win[s][w] != 0;
+      }
+      if (pst != kStNone) {
+        for (int b = 0; b < NB; ++b) {
+          cnt += sm.pool[pst - 1][b];
+          nnz += sm.pool[pst - 1][b] != 0;
         }
       }
-      if (MODE == kMapped)
-        for (int i = tid; i < nk; i += kThreads)
-          if (sg.map_get(i) == kMapDefer) sg.map_set(i, (uint16_t)kMapEmpty);
-      lds_barrier();
-      if (!again) break;
+      const int64_t c = g * K + (MODE != kDense ? (int)sm.slot_kid[s] : s);
+      a.count[c] = cnt;
+      if (cnt) {
+        a.sum_ns[c] = (int64_t)sm.sum[s];
+        a.min_ns[c] = sm.mm[s][0];
+        a.max_ns[c] = sm.mm[s][1];
+        wire += 33u + 5u * nnz;
+      }
     }
-    if (MODE != kDense) {
-      // keys of this range that never occurred: count 0 (their other fields
-      // are not written)
-      for (int i = tid; i < nk; i += kThreads)
-        if (MODE == kHashed ? !((sm.done[i >> 5] >> (i & 31)) & 1u) : sg.map_get(i) == kMapEmpty)
-          a.count[g * K + kb + i] = 0;
-      lds_barrier();
+    // flush: histograms of the present slots (their span is set),
+    // four bins per thread, 16-byte stores
+    for (int it = tid; it < (redo_pass ? 0 : nslot) * (NB / 4); it += kThreads) {
+      const int s = it >> 3, q = it & 7;
+      const uint32_t m = sm.meta[s];
+      const uint32_t pst = (m >> 8) & 0xFFu;
+      if ((m & kDone) || pst == kStPoison || (m & 0xFFu) == kSpanUnset) continue;
+      uint32_t v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int b = 4 * q + j;
+        v[j] = (uint32_t)(b - sg.span_lo(m)) <= sg.span_width(m) ? sm.win[s][sg.win_at(m, b)] : 0u;
+        if (pst != kStNone) v[j] += sm.pool[pst - 1][b];
+      }
+      const int64_t c = g * K + (MODE != kDense ? (int)sm.slot_kid[s] : s);
+      *reinterpret_cast<uint4*>(a.hist + c * NB + 4 * q) = make_uint4(v[0], v[1], v[2], v[3]);
     }
+    lds_barrier();
+    const bool again = sm.poison != 0 || redo_pass;
+    // mark what was written; kernels that ran out of room start over
+    for (int s = tid; s < nslot; s += kThreads) {
+      const uint32_t m = sm.meta[s];
+      if (m & kDone) continue;
+      const bool redo = redo_pass || ((m >> 8) & 0xFFu) == kStPoison;
+      if (MODE == kHashed) {
+        const uint32_t k = sm.slot_kid[s];
+        if (!redo) atomicOr(&sm.done[k >> 5], 1u << (k & 31));
+      } else if (MODE == kMapped) {
+        sg.map_set(sm.slot_kid[s], redo ? (uint16_t)kMapEmpty : (uint16_t)kMapDone);
+      } else if (redo) {
+        sg.slot_reset(s);
+      } else {
+        sm.meta[s] = m | kDone;
+      }
+    }
+    if (MODE == kMapped)
+      for (int i = tid; i < K; i += kThreads)
+        if (sg.map_get(i) == kMapDefer) sg.map_set(i, (uint16_t)kMapEmpty);
+    lds_barrier();
+    if (!again) break;
+  }
+  if (MODE != kDense) {
+    // keys that never occurred: count 0 (their other fields are not written)
+    for (int i = tid; i < K; i += kThreads)
+      if (MODE == kHashed ? !((sm.done[i >> 5] >> (i & 31)) & 1u) : sg.map_get(i) == kMapEmpty)
+        a.count[g * K + i] = 0;
+    lds_barrier();
   }
 
   // per-segment aggregates

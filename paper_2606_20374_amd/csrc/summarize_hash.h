@@ -15,7 +15,7 @@ namespace argus {
 // key << 12 | slot index, or being claimed / deferred in the slot's place;
 // empty is all ones. The table is filled afresh in every pass; keys already
 // written have their bit in done.
-constexpr int kHashIds = ARGUS_MAX_KERNELS;  // every key space is one range in hashed mode
+constexpr int kHashIds = ARGUS_MAX_KERNELS;  // every key space
 constexpr int kHash = 8192, kBucketShift = 32 - 11;
 constexpr uint32_t kHashEmpty = 0xFFFFFFFFu, kTagBits = 12, kTagMask = 0xFFF, kTagBusy = 0xFFE, kTagDefer = 0xFFD;
 
