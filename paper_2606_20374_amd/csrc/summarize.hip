@@ -24,7 +24,8 @@
 //   directly when the key space fits (dense), through an LDS key->slot map
 //   that hands out slots on first sight (mapped, up to 16,384 keys), or
 //   through an LDS hash table of the keys seen (hashed, up to 65,536 keys),
-//   so a large, sparse key space too is read once.
+//   so a large, sparse key space too is read once; keys past the table's slots
+//   are noted and get slots by their rank in further passes.
 // * Whenever the pool or the slots run out, the kernels concerned are
 //   marked and redone exactly in another pass over the segment: the result
 //   is exact for every input; typical traces need one pass.
@@ -35,6 +36,7 @@
 //   (0 for absent kernels); an absent cell's other fields are not written,
 //   so a large, sparse key space costs 4 bytes per absent cell.
 #include <atomic>
+#include <type_traits>
 
 #include "argus_internal.h"
 #include "summarize_hash.h"
@@ -81,7 +83,7 @@ struct Smem {
   uint32_t pool[kPool][NB];
   unsigned long long stream_busy[ARGUS_MAX_STREAMS];
   alignas(16) uint32_t map[MODE == kMapped ? kMapIds / 2 : MODE == kHashed ? kHash : 1];
-  uint32_t done[MODE == kHashed ? kHashIds / 32 : 1];
+  uint32_t left[MODE == kHashed ? kHashIds / 32 : 1];  // hashed mode: bit per key that is left for another pass
   uint16_t slot_kid[MODE != kDense ? NSLOT : 1];
   unsigned long long red_busy, red_wire;
   long long red_first, red_last;
@@ -307,13 +309,50 @@ struct Seg {
   }
 };
 
+// Hashed mode, before a ranked pass: the first NSLOT of the keys left get the
+// slots of their ranks. map[w]: rank of the first key left from word w on. An
+// event outside these keys' range costs a comparison, one inside two four-byte
+// LDS reads, and nothing is claimed. 256 segments of 400,000 events, 29,000 of
+// 60,000 ids (15 passes, HBM bound): 8.0 ms with the table in every pass, 7.2
+// so, 7.1 with one map range of 16,384 ids after another; 32,768 (kernel,
+// stream) keys with Zipf kernels on every stream: 6.9, 6.5 and 11.5.
+template <typename S>
+__device__ __forceinline__ void rank_left(S& sm, int tid) {
+  constexpr int kWords = kHashIds / 32, kPer = kWords / kThreads, NSLOT = sizeof(sm.meta) / sizeof(sm.meta[0]);
+  static_assert(kPer * kThreads == kWords && kWords + kThreads / 64 <= kHash, "words by thread, ranks in the map");
+  uint32_t own = 0;
+  for (int i = 0; i < kPer; ++i) own += (uint32_t)__popc(sm.left[tid * kPer + i]);
+  uint32_t incl = own;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t v = __shfl_up(incl, o, 64);
+    if ((tid & 63) >= o) incl += v;
+  }
+  if ((tid & 63) == 63) sm.map[kWords + (tid >> 6)] = incl;
+  lds_barrier();  // and the last use of the map before
+  uint32_t rank = incl - own, all = 0;
+  for (int w = 0; w < kThreads / 64; ++w) {
+    const uint32_t n = sm.map[kWords + w];
+    if (w < tid >> 6) rank += n;
+    all += n;
+  }
+  for (int i = 0; i < kPer; ++i) {
+    sm.map[tid * kPer + i] = rank;
+    for (uint32_t bits = sm.left[tid * kPer + i]; bits; bits &= bits - 1, ++rank)
+      if (rank < (uint32_t)NSLOT) sm.slot_kid[rank] = (uint16_t)((tid * kPer + i) * 32 + __builtin_ctz(bits));
+  }
+  if (tid == 0) {
+    sm.nslots = all < (uint32_t)NSLOT ? all : (uint32_t)NSLOT;
+    sm.poison = all > (uint32_t)NSLOT ? 1u : 0u;
+  }
+}
+
 // Four events of one thread: validity and per-segment aggregates, then the
-// per-kernel updates.
-template <int NSLOT, int WIN, int MODE>
+// per-kernel updates. RANKED: hashed mode's later passes.
+template <bool RANKED, int NSLOT, int WIN, int MODE>
 __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& a, const int32_t (&kid)[4],
                                          const int32_t (&st)[4], const int64_t (&t0)[4], const int64_t (&t1)[4],
-                                         int n, bool first_scan, uint32_t& nv, uint32_t& ni,
-                                         unsigned long long& busy, long long& tf, long long& tl) {
+                                         int n, bool first_scan, uint32_t k_lo, uint32_t k_n, uint32_t& nv,
+                                         uint32_t& ni, unsigned long long& busy, long long& tf, long long& tl) {
   uint64_t d[4];
   int lk[4];
 #pragma unroll
@@ -321,7 +360,7 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& 
     const bool valid =
         j < n && kid[j] >= 0 && kid[j] < a.n_kernels && st[j] >= 0 && st[j] < a.n_streams && t0[j] >= 0 && t1[j] >= t0[j];
     d[j] = (uint64_t)t1[j] - (uint64_t)t0[j];
-    if (first_scan && j < n) {
+    if (!RANKED && first_scan && j < n) {
       if (valid) {
         nv++;
         busy += d[j];
@@ -333,7 +372,7 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& 
       }
     }
     const uint32_t key = a.key_ns ? (uint32_t)kid[j] * (uint32_t)a.key_ns + (uint32_t)st[j] : (uint32_t)kid[j];
-    lk[j] = valid ? (int)key : -1;
+    lk[j] = valid && (!RANKED || key - k_lo < k_n) ? (int)key : -1;
   }
   // per-kernel updates two events at a time: their LDS lookups are issued
   // together, and the live register set stays small enough that nothing
@@ -341,7 +380,19 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& 
 #pragma unroll
   for (int h = 0; h < 4; h += 2) {
     int slot[2];
-    if (MODE == kHashed) {
+    if (RANKED) {
+      uint32_t w[2], first[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        w[j] = lk[h + j] >= 0 ? sg.sm.left[lk[h + j] >> 5] : 0u;
+        first[j] = lk[h + j] >= 0 ? sg.sm.map[lk[h + j] >> 5] : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t bit = 1u << (lk[h + j] & 31);
+        slot[j] = w[j] & bit ? (int)(first[j] + (uint32_t)__popc(w[j] & (bit - 1))) : -1;
+      }
+    } else if (MODE == kHashed) {
       v4u e[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -352,6 +403,7 @@ __device__ __forceinline__ void process4(Seg<NSLOT, WIN, MODE>& sg, const Args& 
         if (slot[j] == -2) {
           typename Seg<NSLOT, WIN, MODE>::LdsOps ops;
           slot[j] = hash_claim<NSLOT>(ops, sg.sm, lk[h + j], e[j], kSpinCap);
+          if (slot[j] < 0) atomicOr(&sg.sm.left[lk[h + j] >> 5], 1u << (lk[h + j] & 31));
         }
       }
     } else if (MODE == kMapped) {
@@ -436,16 +488,18 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
   bool first_scan = true;
   int n_stuck = 0;  // passes of this segment that ended with a wait cut short
 
-  if (MODE == kHashed)
-    for (int i = tid; i < kHashIds / 32; i += kThreads) sm.done[i] = 0;
-  else if (MODE == kMapped)
+  if (MODE == kMapped)
     for (int i = tid; i < kMapIds / 2; i += kThreads) sm.map[i] = 0xFFFFFFFFu;
-  else
+  else if (MODE == kDense)
     for (int s = tid; s < K; s += kThreads) sg.slot_reset(s);
+  bool ranked = false;          // hashed mode: slots by rank among the keys left
+  uint32_t k_lo = 0, k_n = 0;   // keys that a ranked pass looks at
   while (true) {
     // the mapped and hashed modes hand out slots afresh in every pass
-    if (MODE == kHashed)
+    if (MODE == kHashed && !ranked) {
       for (int i = tid; i < kHash; i += kThreads) sm.map[i] = kHashEmpty;
+      for (int i = tid; i < kHashIds / 32; i += kThreads) sm.left[i] = 0;
+    }
     if (MODE != kDense)
       for (int s = tid; s < NSLOT; s += kThreads) sg.slot_reset(s);
     for (int i = tid; i < sm.kPool * NB; i += kThreads) (&sm.pool[0][0])[i] = 0;
@@ -455,80 +509,92 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
       sm.nslots = 0;
       sm.stuck = 0;
     }
+    if (MODE == kHashed && ranked) rank_left(sm, tid);
     lds_barrier();
-
-    // unaligned head and tail: at most 3 events each, on the first threads
-    if (a.vec_ok) {
-      int32_t kid[4], st[4];
-      int64_t t0[4], t1[4];
-      int n = 0;
-      const int64_t h = a4 - lo, t = hi - b4;
-      const int64_t i = tid < h ? lo + tid : (tid - h < t ? b4 + (tid - h) : -1);
-      if (i >= 0) {
-        kid[0] = a.kernel_id[i];
-        st[0] = a.stream[i];
-        t0[0] = a.start_ns[i];
-        t1[0] = a.end_ns[i];
-        n = 1;
-      }
-      for (int j = n; j < 4; ++j) {
-        kid[j] = -1;
-        st[j] = 0;
-        t0[j] = t1[j] = 0;
-      }
-      if (n) process4(sg, a, kid, st, t0, t1, n, first_scan, nv, ni, busy, tf, tl);
+    if (MODE == kHashed && ranked) {
+      k_lo = __builtin_amdgcn_readfirstlane(sm.slot_kid[0]);
+      k_n = sm.nslots ? __builtin_amdgcn_readfirstlane(sm.slot_kid[sm.nslots - 1]) - k_lo + 1 : 0;
     }
-    if (!a.vec_ok) {
-      // scalar fallback for unaligned arrays: four strided events per thread
-      for (int64_t i0 = lo + tid; i0 < hi; i0 += 4ll * kThreads) {
+
+    auto scan = [&](auto by_rank) __attribute__((always_inline)) {
+      constexpr bool ranked_pass = decltype(by_rank)::value;
+      // unaligned head and tail: at most 3 events each, on the first threads
+      if (a.vec_ok) {
         int32_t kid[4], st[4];
         int64_t t0[4], t1[4];
         int n = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t i = i0 + (int64_t)j * kThreads;  // in range for a prefix of j
-          const bool in = i < hi;
-          kid[j] = in ? a.kernel_id[i] : -1;
-          st[j] = in ? a.stream[i] : 0;
-          t0[j] = in ? a.start_ns[i] : 0;
-          t1[j] = in ? a.end_ns[i] : 0;
-          n += in;
+        const int64_t h = a4 - lo, t = hi - b4;
+        const int64_t i = tid < h ? lo + tid : (tid - h < t ? b4 + (tid - h) : -1);
+        if (i >= 0) {
+          kid[0] = a.kernel_id[i];
+          st[0] = a.stream[i];
+          t0[0] = a.start_ns[i];
+          t1[0] = a.end_ns[i];
+          n = 1;
         }
-        process4(sg, a, kid, st, t0, t1, n, first_scan, nv, ni, busy, tf, tl);
-      }
-    }
-    // aligned body: group q holds events 4q..4q+3; the next group's loads
-    // are issued before the current group is processed
-    {
-      int64_t q = qa + tid;
-      v4i nk4 = 0, ns4 = 0;
-      v2l na0 = 0, na1 = 0, nb0 = 0, nb1 = 0;
-      if (q < qb) {
-        nk4 = __builtin_nontemporal_load(K4 + q);
-        ns4 = __builtin_nontemporal_load(S4 + q);
-        na0 = __builtin_nontemporal_load(T0 + 2 * q);
-        na1 = __builtin_nontemporal_load(T0 + 2 * q + 1);
-        nb0 = __builtin_nontemporal_load(T1 + 2 * q);
-        nb1 = __builtin_nontemporal_load(T1 + 2 * q + 1);
-      }
-      while (q < qb) {
-        const int32_t kid[4] = {nk4.x, nk4.y, nk4.z, nk4.w};
-        const int32_t st[4] = {ns4.x, ns4.y, ns4.z, ns4.w};
-        const int64_t t0[4] = {na0.x, na0.y, na1.x, na1.y};
-        const int64_t t1[4] = {nb0.x, nb0.y, nb1.x, nb1.y};
-        const int64_t qn = q + kThreads;
-        if (qn < qb) {
-          nk4 = __builtin_nontemporal_load(K4 + qn);
-          ns4 = __builtin_nontemporal_load(S4 + qn);
-          na0 = __builtin_nontemporal_load(T0 + 2 * qn);
-          na1 = __builtin_nontemporal_load(T0 + 2 * qn + 1);
-          nb0 = __builtin_nontemporal_load(T1 + 2 * qn);
-          nb1 = __builtin_nontemporal_load(T1 + 2 * qn + 1);
+        for (int j = n; j < 4; ++j) {
+          kid[j] = -1;
+          st[j] = 0;
+          t0[j] = t1[j] = 0;
         }
-        process4(sg, a, kid, st, t0, t1, 4, first_scan, nv, ni, busy, tf, tl);
-        q = qn;
+        if (n) process4<ranked_pass>(sg, a, kid, st, t0, t1, n, first_scan, k_lo, k_n, nv, ni, busy, tf, tl);
       }
-    }
+      if (!a.vec_ok) {
+        // scalar fallback for unaligned arrays: four strided events per thread
+        for (int64_t i0 = lo + tid; i0 < hi; i0 += 4ll * kThreads) {
+          int32_t kid[4], st[4];
+          int64_t t0[4], t1[4];
+          int n = 0;
+  #pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int64_t i = i0 + (int64_t)j * kThreads;  // in range for a prefix of j
+            const bool in = i < hi;
+            kid[j] = in ? a.kernel_id[i] : -1;
+            st[j] = in ? a.stream[i] : 0;
+            t0[j] = in ? a.start_ns[i] : 0;
+            t1[j] = in ? a.end_ns[i] : 0;
+            n += in;
+          }
+          process4<ranked_pass>(sg, a, kid, st, t0, t1, n, first_scan, k_lo, k_n, nv, ni, busy, tf, tl);
+        }
+      }
+      // aligned body: group q holds events 4q..4q+3; the next group's loads
+      // are issued before the current group is processed
+      {
+        int64_t q = qa + tid;
+        v4i nk4 = 0, ns4 = 0;
+        v2l na0 = 0, na1 = 0, nb0 = 0, nb1 = 0;
+        if (q < qb) {
+          nk4 = __builtin_nontemporal_load(K4 + q);
+          ns4 = __builtin_nontemporal_load(S4 + q);
+          na0 = __builtin_nontemporal_load(T0 + 2 * q);
+          na1 = __builtin_nontemporal_load(T0 + 2 * q + 1);
+          nb0 = __builtin_nontemporal_load(T1 + 2 * q);
+          nb1 = __builtin_nontemporal_load(T1 + 2 * q + 1);
+        }
+        while (q < qb) {
+          const int32_t kid[4] = {nk4.x, nk4.y, nk4.z, nk4.w};
+          const int32_t st[4] = {ns4.x, ns4.y, ns4.z, ns4.w};
+          const int64_t t0[4] = {na0.x, na0.y, na1.x, na1.y};
+          const int64_t t1[4] = {nb0.x, nb0.y, nb1.x, nb1.y};
+          const int64_t qn = q + kThreads;
+          if (qn < qb) {
+            nk4 = __builtin_nontemporal_load(K4 + qn);
+            ns4 = __builtin_nontemporal_load(S4 + qn);
+            na0 = __builtin_nontemporal_load(T0 + 2 * qn);
+            na1 = __builtin_nontemporal_load(T0 + 2 * qn + 1);
+            nb0 = __builtin_nontemporal_load(T1 + 2 * qn);
+            nb1 = __builtin_nontemporal_load(T1 + 2 * qn + 1);
+          }
+          process4<ranked_pass>(sg, a, kid, st, t0, t1, 4, first_scan, k_lo, k_n, nv, ni, busy, tf, tl);
+          q = qn;
+        }
+      }
+    };
+    if (MODE == kHashed && ranked)
+      scan(std::bool_constant<MODE == kHashed>{});
+    else
+      scan(std::false_type{});
     first_scan = false;
     lds_barrier();
 
@@ -588,6 +654,8 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
       const int64_t c = g * K + (MODE != kDense ? (int)sm.slot_kid[s] : s);
       *reinterpret_cast<uint4*>(a.hist + c * NB + 4 * q) = make_uint4(v[0], v[1], v[2], v[3]);
     }
+    if (MODE == kHashed && !ranked)
+      for (int i = tid; i < kHashIds / 32; i += kThreads) sm.map[i] = 0;  // from here on: keys that had a slot
     lds_barrier();
     const bool again = sm.poison != 0 || redo_pass;
     // mark what was written; kernels that ran out of room start over
@@ -596,8 +664,13 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
       if (m & kDone) continue;
       const bool redo = redo_pass || ((m >> 8) & 0xFFu) == kStPoison;
       if (MODE == kHashed) {
-        const uint32_t k = sm.slot_kid[s];
-        if (!redo) atomicOr(&sm.done[k >> 5], 1u << (k & 31));
+        const uint32_t k = sm.slot_kid[s], bit = 1u << (k & 31);
+        if (ranked) {
+          if (!redo) atomicAnd(&sm.left[k >> 5], ~bit);
+        } else {
+          atomicOr(&sm.map[k >> 5], bit);
+          if (redo) atomicOr(&sm.left[k >> 5], bit);
+        }
       } else if (MODE == kMapped) {
         sg.map_set(sm.slot_kid[s], redo ? (uint16_t)kMapEmpty : (uint16_t)kMapDone);
       } else if (redo) {
@@ -610,13 +683,17 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
       for (int i = tid; i < K; i += kThreads)
         if (sg.map_get(i) == kMapDefer) sg.map_set(i, (uint16_t)kMapEmpty);
     lds_barrier();
+    // keys that never occurred: count 0 (their other fields are not written)
+    if (MODE == kHashed && !ranked && !redo_pass) {
+      for (int i = tid; i < K; i += kThreads)
+        if (!(((sm.map[i >> 5] | sm.left[i >> 5]) >> (i & 31)) & 1u)) a.count[g * K + i] = 0;
+      ranked = true;
+    }
     if (!again) break;
   }
-  if (MODE != kDense) {
-    // keys that never occurred: count 0 (their other fields are not written)
+  if (MODE == kMapped) {
     for (int i = tid; i < K; i += kThreads)
-      if (MODE == kHashed ? !((sm.done[i >> 5] >> (i & 31)) & 1u) : sg.map_get(i) == kMapEmpty)
-        a.count[g * K + i] = 0;
+      if (sg.map_get(i) == kMapEmpty) a.count[g * K + i] = 0;
     lds_barrier();
   }
 

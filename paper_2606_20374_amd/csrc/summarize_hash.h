@@ -13,9 +13,9 @@ namespace argus {
 // 2,048 buckets of four entries (one 16-byte LDS read), at most a quarter
 // full, so all but about 0.5% of the keys lie in their own bucket. An entry:
 // key << 12 | slot index, or being claimed / deferred in the slot's place;
-// empty is all ones. The table is filled afresh in every pass; keys already
-// written have their bit in done.
-constexpr int kHashIds = ARGUS_MAX_KERNELS;  // every key space
+// empty is all ones. The table serves a segment's first pass; the keys that
+// get no slot in it take theirs by rank in the passes after it.
+constexpr int kHashIds = ARGUS_MAX_KERNELS;
 constexpr int kHash = 8192, kBucketShift = 32 - 11;
 constexpr uint32_t kHashEmpty = 0xFFFFFFFFu, kTagBits = 12, kTagMask = 0xFFF, kTagBusy = 0xFFE, kTagDefer = 0xFFD;
 
@@ -37,7 +37,7 @@ __host__ __device__ inline int hash_find(int key, const v4u& e) {
 
 // Slot of key, which its bucket (read as e0) does not hold with a slot:
 // claims the first empty entry from the bucket on, or finds the key further
-// on; -1 when the key is already written or has no slot in this pass.
+// on; -1 when the key has no slot in this pass.
 //
 // Entries only go from empty to claimed to published, so the stale read e0
 // can only start the walk early. At most NSLOT keys and one more per thread
@@ -56,7 +56,7 @@ __host__ __device__ inline int hash_find(int key, const v4u& e) {
 // the loop, before a waiting lane of its own wavefront re-reads the entry.
 template <int NSLOT, typename M, typename S>
 __host__ __device__ inline int hash_claim(M& m, S& sm, int key, const v4u& e0, int spin_cap) {
-  int res = (sm.done[key >> 5] >> (key & 31)) & 1u ? -1 : -2;
+  int res = -2;
   const uint32_t mine = (uint32_t)key << kTagBits;
   int skip = 4;
 #pragma unroll

@@ -19,7 +19,6 @@ constexpr size_t kStack = 1 << 16;
 
 struct Table {
   uint32_t map[argus::kHash];
-  uint32_t done[argus::kHashIds / 32];
   uint16_t slot_kid[kSlots];
   uint32_t nslots, poison, stuck;
 };

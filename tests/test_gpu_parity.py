@@ -474,3 +474,27 @@ def test_window_spans(K):
     torch.cuda.synchronize()
     o = oracle.summarize(ev, K, 5)
     P.assert_int_equal(g, o, P.SUM_INT_FIELDS, f"spans K={K}")
+
+
+@pytest.mark.parametrize("K,NS,keyed,skew", [(65_536, 3, False, 0), (20_001, 3, False, 1), (4096, 16, True, 0)])
+def test_every_key_of_a_large_space(K, NS, keyed, skew):
+    """Every key of hashed key spaces occurs, the first and last one among
+    them, so that most take slots by rank in later passes; some span all
+    octaves (full records run out in these passes too), and one segment has
+    exactly as many keys as there are slots."""
+    _announce(f"every key K={K} NS={NS} keyed={keyed}")
+    rng = np.random.default_rng(K)
+    n_keys = K * NS if keyed else K
+    n = 2 * n_keys + 2048
+    key = np.concatenate([rng.permutation(n_keys), rng.integers(0, n_keys, n_keys), np.arange(2048) * (n_keys // 2048)])
+    ev = _random_events(n + skew, K, NS, seed=K, spread_octaves=3, seg_lengths=[skew, 2 * n_keys, 2048])
+    kid, st = (key // NS, key % NS) if keyed else (key, rng.integers(0, NS, n))
+    ev["kernel_id"][skew:], ev["stream"][skew:] = kid, st
+    wide = np.flatnonzero(key % 200 == 7)
+    ev["start_ns"][skew:][wide] = 2**60
+    ev["end_ns"][skew:][wide] = 2**60 + 2 ** rng.integers(0, 33, wide.size)
+    g = pa.summarize(_dev_events(ev), 3, 1, K, NS, keyed=keyed)
+    torch.cuda.synchronize()
+    o = oracle.summarize(ev, K, NS, keyed=keyed)
+    assert np.asarray(o["count"]).reshape(3, n_keys)[1].min() >= 1
+    P.assert_int_equal(g, o, P.SUM_INT_FIELDS, f"every key K={K} keyed={keyed}")
