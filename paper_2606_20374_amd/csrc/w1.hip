@@ -684,17 +684,24 @@ __global__ __launch_bounds__(NT) void w1_score(W1Args a) {
 // 1,000 ranks: 2,778 / 3,199 / 3,429 / 4,151 us with w1_score (256 threads),
 // 214 / 441 / 986 / 2,704 us with pairs; n^2 overtakes the sort between 1,024
 // and 2,048 ranks (16,000 cycles per point there, pairs 32,000).
+// Past 512 ranks and up to kPairFew (step, kernel) pairs, at most one
+// workgroup per CU: 16 wavefronts, a rank per thread, as four with four ranks
+// each leave a SIMD one wavefront to wait with. 1,024 ranks, 1 / 8 / 256 / 300
+// kernels: 467 / 492 / 577 / 761 us with four wavefronts, 353 / 373 / 459 /
+// 774 with 16 (w1_score: 355 / 498 / 663 / 1,034).
 constexpr int kPairRanks = 1024;
+constexpr int64_t kPairFew = 256;
 
 template <int NT, int V>
 __global__ __launch_bounds__(NT) void w1_score_pairs(W1Args a) {
-  static_assert(NT == 256 && V <= 4, "row buffer");
+  static_assert((NT == 256 && V <= 4) || (NT == 1024 && V == 1), "row buffer");
+  constexpr bool kByCount = NT == 256 && V == 1;  // quartiles by counting
   constexpr int kStageWords = 8192;  // 32 KB: at least 16 rows
   static_assert(NT * V <= kPairRanks, "rows");
   constexpr int NW = NT / 64;
   __shared__ alignas(16) uint32_t stage[kStageWords];
   __shared__ double wts[ARGUS_MAX_W1_GRID];
-  __shared__ uint64_t keys[V == 1 ? NT : 1];
+  __shared__ uint64_t keys[kByCount ? NT : 1];
   __shared__ SelShared<2> sel;
   __shared__ unsigned long long mn_sh, mx_sh, pick[2];
   __shared__ uint32_t nf_sh, wave_n[V * NW];
@@ -806,7 +813,7 @@ __global__ __launch_bounds__(NT) void w1_score_pairs(W1Args a) {
 #pragma unroll
   for (int j = 0; j < V; ++j) key[j] = (uint64_t)__double_as_longlong(acc[j] / norm);
   double a1, a3;
-  if constexpr (V == 1) {
+  if constexpr (kByCount) {
     // few scores: each one's place by counting (ties by rank)
     if (present(0)) keys[place[0]] = key[0];
     __syncthreads();
@@ -979,6 +986,7 @@ hipError_t launch_w1(const W1Launch& l, hipStream_t st) {
   const dim3 blocks((unsigned)SK);
   if (R <= 256) hipLaunchKernelGGL((w1_score_pairs<256, 1>), blocks, dim3(256), 0, st, wa);
   else if (R <= 512) hipLaunchKernelGGL((w1_score_pairs<256, 2>), blocks, dim3(256), 0, st, wa);
+  else if (R <= kPairRanks && SK <= kPairFew) hipLaunchKernelGGL((w1_score_pairs<1024, 1>), blocks, dim3(1024), 0, st, wa);
   else if (R <= kPairRanks) hipLaunchKernelGGL((w1_score_pairs<256, 4>), blocks, dim3(256), 0, st, wa);
   else if (R <= 2048) launch_score<1024, 2>(wa, st);
   else if (R <= 4096) launch_score<1024, 4>(wa, st);

@@ -216,7 +216,8 @@ def test_w1_random_cluster_sets(R, S, K, seed):
                                  (257, 40), (511, 8), (513, 64), (1023, 9), (1024, 64), (1025, 64)])
 def test_w1_rank_and_grid_edges(R, G):
     """Rank counts around the limits of the pairwise score kernel (256 threads
-    of 1, 2 or 4 ranks, four-word rows; the sorting kernel past 1,024) and of
+    of 1 or 2 ranks or, with few kernels, 1,024 of one, four-word rows; the
+    sorting kernel past 1,024) and of
     the CDF kernel's lane packing (64), grids that its workgroups split
     unevenly, absent and malformed cells, kernel counts that leave wavefronts
     part empty."""
@@ -228,6 +229,24 @@ def test_w1_rank_and_grid_edges(R, G):
     torch.cuda.synchronize()
     ow = oracle.w1(ncl, cnt, a, b, R, S, K, grid=G, min_ranks=2)
     assert_w1_equal(gw, ow, R, S, K, f"ranks {R} grid {G}")
+
+
+@pytest.mark.parametrize("R", [513, 769, 1024])
+@pytest.mark.parametrize("K", [128, 129])
+def test_w1_pairs_by_workgroups(R, K):
+    """Up to 256 (step, kernel) pairs of more than 512 ranks take a rank per
+    thread, more of them four: the last of the one and the first of the other."""
+    _announce(f"w1 pairs ranks {R} kernels {K}")
+    rng = np.random.default_rng(R + K)
+    S, G, few = 2, 9, 5
+    ncl, cnt, a, b = _random_clusters(rng, R, S, few, p_absent=0.2, outliers=0.1)
+    ks = np.arange(K) % few  # kernels repeat
+    ncl = ncl.reshape(R, S, few)[:, :, ks].reshape(-1)
+    cnt, a, b = (x.reshape(R, S, few, MAXC)[:, :, ks].reshape(-1, MAXC) for x in (cnt, a, b))
+    gw = pa.w1(_dev_clusters(ncl, cnt, a, b), R, S, K, grid=G)
+    torch.cuda.synchronize()
+    ow = oracle.w1(ncl, cnt, a, b, R, S, K, grid=G)
+    assert_w1_equal(gw, ow, R, S, K, f"ranks {R} kernels {K}")
 
 
 def test_w1_malformed_records_are_reported():
