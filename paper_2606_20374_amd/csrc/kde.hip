@@ -2273,11 +2273,12 @@ constexpr int kRouteThreads = 512;
 constexpr int kLaneClasses = 512;                          // 32 grid-size x 16 duration-count classes
 constexpr int kWideClasses = 384;                          // 24 x 16 for the wide pass
 constexpr int kHeavyAt = kLaneClasses + kWideClasses;      // 32 heavy classes, most durations first
-constexpr int kTier0At = kHeavyAt + 32;                    // 96 tier-0 classes, costliest first
+constexpr int kTier0At = kHeavyAt + 32;                    // tier-0 classes, costliest first
+constexpr int kTier0Classes = 25;
 constexpr int kClasses = 1024;                             // all, two per thread
 constexpr uint16_t kNoClass = 0xFFFF;
 constexpr int kOrderPer = 16;  // cells per thread and round in kde_order_kernel
-static_assert(kClasses == 2 * kRouteThreads && kTier0At + 96 == kClasses, "class scan");
+static_assert(kClasses == 2 * kRouteThreads && kTier0At + kTier0Classes <= kClasses, "class scan");
 static_assert(kLaneClasses % 128 == 0 && kWideClasses % 128 == 0, "class totals by wavefront");
 static_assert(((kLaneG - 1) >> 1) * 16 + ((kLaneN - 1) >> 4) < kLaneClasses, "lane classes");
 static_assert(((kLaneGW - 65) >> 3) * 16 + ((kLaneN - 1) >> 4) < kWideClasses, "wide classes");
@@ -2287,6 +2288,11 @@ static_assert(((kLaneGW - 65) >> 3) * 16 + ((kLaneN - 1) >> 4) < kWideClasses, "
 // quarter octaves of their duration count and tier-0 cells by n + 2 G, which
 // follows their cost, largest first, so that the cells claimed last are
 // short: in kernel-id order the last claims could hold the largest ones.
+// From n + 2 G = 768 on, mostly grids that tier 0 hands on, cells stay in
+// kernel-id order: ordered up to 3,040 they were slower on wide durations
+// (lognormal with sigma 2: 205,000 cells of 195 durations 13.16 ms, 12.94 so;
+// sigma 1: 5.19 and 4.91 ms). With no order at all cells short of it lose more
+// (100 rank-steps of 100,000 Zipf events over 500 ids: 543 us so, 583 then).
 __device__ __forceinline__ uint16_t route_code(const CellMeta& m, const uint32_t* th, int sh, bool no_lanes) {
   if (m.n == 0 || m.off < 0) return kNoClass;
   if (m.n >= kBlockMin) {
@@ -2300,7 +2306,7 @@ __device__ __forceinline__ uint16_t route_code(const CellMeta& m, const uint32_t
     if (G <= kLaneGW) return (uint16_t)(kLaneClasses + ((G - 65) >> 3) * 16 + (int)((m.n - 1) >> 4));
   }
   const int cost = ((int)m.n + 2 * G) >> 5;
-  return (uint16_t)(kTier0At + 95 - (cost < 95 ? cost : 95));
+  return (uint16_t)(kTier0At + kTier0Classes - 1 - (cost < kTier0Classes ? cost : kTier0Classes - 1));
 }
 
 // Contiguous range of cells of workgroup b out of nb.
