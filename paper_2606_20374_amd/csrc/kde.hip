@@ -13,16 +13,18 @@
 //                        writes them as aligned 64-byte groups. HBM bound:
 //                        24 B read and 8 B written per event.
 //   kde_route_kernel,    every cell routed once: empty cells written, heavy
-//   kde_order_kernel cells to the workgroup tier, large or wide-grid
-//                        cells to tier 0, the rest to the lane passes in
-//                        cost-class order (grid size x duration count).
+//   kde_order_kernel     cells to the workgroup tier, large or wide-grid
+//                        cells to tier 0, the rest to the lane passes (every
+//                        cell but the heavy ones to tier 0 where there are
+//                        few), each list in cost-class order.
 //   kde_lane_kernel<64>, one cell per lane, 64 cells per wavefront (grids of
 //   kde_lane_kernel<256> up to 64 / 65-256 points, up to 255 durations).
 //   kde_block_kernel     one 128-thread workgroup per cell of 2,048 or more
 //                        durations.
-//   kde_cell_kernel<0>   one wavefront per cell, cells claimed 64 at a time
-//                        with their summaries, n^(-1/5) and (for cells of up to
-//                        256 durations) the next cell's durations prefetched
+//   kde_cell_kernel<0>   one wavefront per cell, cells dealt out in cost order
+//                        (the last quarter of long lists off a queue), up to
+//                        64 summaries read at once, n^(-1/5) and (for cells of
+//                        up to 256 durations) the next cell's durations prefetched
 //                        while the current cell is processed: grid histogram
 //                        in LDS, exact bandwidth, integer-weight density
 //                        (sparse over occupied grid points when that is

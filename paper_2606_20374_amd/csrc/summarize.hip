@@ -237,9 +237,6 @@ struct Seg {
     }
   }
 
-  // mmv: min and max of the slot as read before this event (possibly stale:
-  // min only falls and max only rises, so a stale read can only cause an
-  // extra atomic, never a missed one)
   // Span of the window in meta word m (its first bin set): first bin, width
   // (last bin - first), and the place of bin b of the span in the window.
   __device__ __forceinline__ static int span_lo(uint32_t m) { return (int)(m & 0xFFu); }
@@ -253,9 +250,9 @@ struct Seg {
 
   // Mapped and hashed modes: widen the span of slot's window to hold bin b
   // (m: its meta word, updated to the newest read); false when that would pass
-  // WIN octaves. Spans only
-  // widen and a state changes at most twice, and a failed swap means that
-  // another lane's succeeded, so the loop ends after a bounded count.
+  // WIN octaves. Spans only widen and a state changes at most twice, and a
+  // failed swap means that another lane's succeeded, so the loop ends after a
+  // bounded count.
   __device__ bool span_widen(int slot, uint32_t& m, int b) {
     while (true) {
       const bool unset = (m & 0xFFu) == kSpanUnset;
@@ -273,6 +270,9 @@ struct Seg {
     }
   }
 
+  // mmv: min and max of the slot as read before this event (possibly stale:
+  // min only falls and max only rises, so a stale read can only cause an
+  // extra atomic, never a missed one)
   __device__ __forceinline__ void slot_add(int slot, uint32_t m, uint64_t d, const v2l& mmv) {
     if (m & kDone) return;
     const int b = octave_bin(d);
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
           int32_t kid[4], st[4];
           int64_t t0[4], t1[4];
           int n = 0;
-  #pragma unroll
+#pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int64_t i = i0 + (int64_t)j * kThreads;  // in range for a prefix of j
             const bool in = i < hi;

@@ -6,8 +6,9 @@ sides decide them with exact integer comparisons); mean, std and CV (double)
 and z (float) within 1e-5 relative. Cases: closed-form outlier groups, CV
 boundaries, identical and all-zero groups, routing / membership / domain
 rules with malformed and duplicate listings, random groups over ragged event
-counts up to 65,536 ranks, and the medium trace through the GPU chain
-summarize -> l2. The full-size workloads are checked in test_gpu_full.py.
+counts up to 65,536 ranks, the medium trace through the GPU chain
+summarize -> l2, group sizes and means at the kernels' limits, sparse
+listings, small and large groups of one dimension, and few ranks. The full-size workloads are checked in test_gpu_full.py.
 """
 import numpy as np
 import pytest
@@ -132,11 +133,12 @@ def test_l2_medium_chain():
                                           (32, 513, 1), (33, 300, 1), (191, 70, 1), (193, 1, 1), (512, 3, 1),
                                           (8, 65, 2**13), (40, 65, 2**13), (200, 9, 2**13)])
 def test_l2_group_size_edges(size, E, scale):
-    """Group sizes around the batch (8), the means kept between the passes
-    (24 to a wavefront), the small / large boundary (32) and eight wavefronts'
-    keep (192); event counts around the 64-lane and 2,048-id tiles; scale 2^13
-    puts the means of some members beyond 2^32 ns and some sums beyond 2^53
-    (the wide arithmetic) next to narrow ones."""
+    """Groups of one size, every listing valid: sizes around the batch (8), the
+    means kept between the passes (24 to a wavefront), the small / large
+    boundary (32) and eight wavefronts' keep (192); event counts around the
+    64-lane and 2,048-id tiles; scale 2^13 puts the means of some members
+    beyond 2^32 ns and some sums beyond 2^53 (the wide arithmetic) next to
+    narrow ones. Sparse listings and mixed sizes have tests of their own below."""
     _announce(f"l2 group size {size}, {E} events, scale {scale}")
     rng = np.random.default_rng(size * 7919 + E)
     G = 11  # more groups than one workgroup's wavefronts

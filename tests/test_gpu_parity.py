@@ -149,7 +149,8 @@ def test_malformed_segments_raise_device_status():
 
 
 def test_large_kernel_id_space_multi_range():
-    _announce("K=8200 id ranges")
+    """The skew trace's ids, past the slots: the mapped key space."""
+    _announce("K=8200 mapped ids")
     t = tracegen.make("skew", n_ranks=6, n_steps=2, events_per_seg=30_000)
     g, o = _summarize_both(t.fill_host(), 6, 2, t.cfg.n_kernels, t.cfg.n_streams)
     P.assert_int_equal(g, o, P.SUM_INT_FIELDS, "skew-small")
@@ -192,6 +193,8 @@ def test_mapped_slot_overflow():
 
 
 def test_mapped_several_id_ranges():
+    """More ids than the map holds: the hashed key space, with more ids in a
+    segment than slots."""
     _announce("hashed ids: id space of 40,000")
     K = 40_000
     ev = _random_events(50_000, K, 8, seed=22, seg_lengths=[20_000, 0, 30_000, 0])
