@@ -611,7 +611,7 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(Args a) {
 
     // flush: the count of every slot; sum, min, max and wire size of the
     // present ones
-    const int nslot = MODE != kDense ? (int)(sm.nslots < (uint32_t)NSLOT ? sm.nslots : NSLOT) : K;
+    const int nslot = MODE != kDense ? (int)(sm.nslots < (uint32_t)NSLOT ? sm.nslots : NSLOT) : (K < NSLOT ? K : NSLOT);
     for (int s = tid; s < (redo_pass ? 0 : nslot); s += kThreads) {
       const uint32_t m = sm.meta[s];
       const uint32_t pst = (m >> 8) & 0xFFu;
