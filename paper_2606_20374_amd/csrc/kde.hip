@@ -2276,7 +2276,8 @@ constexpr int kLaneClasses = 512;                          // 32 grid-size x 16 
 constexpr int kWideClasses = 384;                          // 24 x 16 for the wide pass
 constexpr int kHeavyAt = kLaneClasses + kWideClasses;      // 32 heavy classes, most durations first
 constexpr int kTier0At = kHeavyAt + 32;                    // tier-0 classes, costliest first
-constexpr int kTier0Classes = 25;
+constexpr int kTier0Classes = 96;
+constexpr int kOrderG = 384;                               // grid points up to which tier-0 cells are ordered
 constexpr int kClasses = 1024;                             // all, two per thread
 constexpr uint16_t kNoClass = 0xFFFF;
 constexpr int kOrderPer = 16;  // cells per thread and round in kde_order_kernel
@@ -2290,11 +2291,13 @@ static_assert(((kLaneGW - 65) >> 3) * 16 + ((kLaneN - 1) >> 4) < kWideClasses, "
 // quarter octaves of their duration count and tier-0 cells by n + 2 G, which
 // follows their cost, largest first, so that the cells claimed last are
 // short: in kernel-id order the last claims could hold the largest ones.
-// From n + 2 G = 768 on, mostly grids that tier 0 hands on, cells stay in
-// kernel-id order: ordered up to 3,040 they were slower on wide durations
-// (lognormal with sigma 2: 205,000 cells of 195 durations 13.16 ms, 12.94 so;
-// sigma 1: 5.19 and 4.91 ms). With no order at all cells short of it lose more
-// (100 rank-steps of 100,000 Zipf events over 500 ids: 543 us so, 583 then).
+// Grids of more than kOrderG points, most of which tier 0 hands on, come first
+// and stay in kernel-id order: ordered by their cost too they were slower
+// (lognormal durations with sigma 1: 205,000 cells of 195 durations 5.19 ms,
+// 4.90 so; sigma 2: 13.10 and 12.99 ms). Ordering none from n + 2 G = 768 on
+// cost narrow cells of many durations their order (45,000 cells of 730: 812
+// us, 759 so), and no order at all cost short ones (50,000 cells of 200: 583
+// us, 550 so).
 __device__ __forceinline__ uint16_t route_code(const CellMeta& m, const uint32_t* th, int sh, bool no_lanes) {
   if (m.n == 0 || m.off < 0) return kNoClass;
   if (m.n >= kBlockMin) {
@@ -2308,7 +2311,7 @@ __device__ __forceinline__ uint16_t route_code(const CellMeta& m, const uint32_t
     if (G <= kLaneGW) return (uint16_t)(kLaneClasses + ((G - 65) >> 3) * 16 + (int)((m.n - 1) >> 4));
   }
   const int cost = ((int)m.n + 2 * G) >> 5;
-  return (uint16_t)(kTier0At + kTier0Classes - 1 - (cost < kTier0Classes ? cost : kTier0Classes - 1));
+  return (uint16_t)(kTier0At + kTier0Classes - 1 - (G <= kOrderG && cost < kTier0Classes ? cost : kTier0Classes - 1));
 }
 
 // Contiguous range of cells of workgroup b out of nb.
