@@ -26,9 +26,9 @@
 // (10,240 ranks x 2,048 events, TP / PP / DP / EP groups of 8 / 8 / 160 / 8):
 // 996 us with one wavefront per group and 64 consecutive event ids, whose
 // members were read one after another (four dependent loads each, twice) and
-// whose 160-member groups were the tail; 363 us now, 1014 -> 391 us per call.
-// Of that, the loads are about 90 us, the z and flag stores 75 us, the group
-// outputs 30 us. The unrolled exact arithmetic of an earlier form (16,400
+// whose 160-member groups were the tail; 339 us now, 1,014 -> 388 us per call.
+// The loads are about 90 us of it, the z and flag stores 75 us, the group
+// outputs 30 us, timed by leaving each out. The unrolled exact arithmetic of an earlier form (16,400
 // instructions) did not fit the instruction cache and ran at half the speed.
 #include "argus_internal.h"
 
