@@ -341,10 +341,9 @@ def main():
         torch.cuda.synchronize()
         c_ms = e0.elapsed_time(e1) / args.compact_reps
         assert int(comp["dev_status"].item()) == 0
-        # read: count of every cell, hist of the present ones, sum / min /
-        # max of the present ones (twice: sizing and writing); written: the
-        # records and the segment offsets
-        c_bytes = 4 * G * K * 2 + present * (128 * 2 + 24) + total + 16 * G
+        # read once: count of every cell, hist, sum, min and max of the present
+        # ones; written: the records and the segment offsets
+        c_bytes = 4 * G * K + present * (128 + 24) + total + 8 * G
         result["compact"] = {
             "ms": c_ms, "bytes": total, "bytes_per_rank_step": total / G,
             "raw_bytes_per_rank_step": 24 * trace.n_events / G,
