@@ -316,6 +316,8 @@ struct Seg {
 // 60,000 ids (15 passes, HBM bound): 8.0 ms with the table in every pass, 7.2
 // so, 7.1 with one map range of 16,384 ids after another; 32,768 (kernel,
 // stream) keys with Zipf kernels on every stream: 6.9, 6.5 and 11.5.
+// A thread's keys past the last slot are counted by their words' set bits, not
+// one by one (512 segments of 20,000 events, 32,768 keys: 859 -> 759 us).
 template <typename S>
 __device__ __forceinline__ void rank_left(S& sm, int tid) {
   constexpr int kWords = kHashIds / 32, kPer = kWords / kThreads, NSLOT = sizeof(sm.meta) / sizeof(sm.meta[0]);
@@ -337,8 +339,10 @@ __device__ __forceinline__ void rank_left(S& sm, int tid) {
   }
   for (int i = 0; i < kPer; ++i) {
     sm.map[tid * kPer + i] = rank;
-    for (uint32_t bits = sm.left[tid * kPer + i]; bits; bits &= bits - 1, ++rank)
-      if (rank < (uint32_t)NSLOT) sm.slot_kid[rank] = (uint16_t)((tid * kPer + i) * 32 + __builtin_ctz(bits));
+    uint32_t bits = sm.left[tid * kPer + i], at = rank;
+    rank += (uint32_t)__popc(bits);
+    for (; bits && at < (uint32_t)NSLOT; bits &= bits - 1, ++at)
+      sm.slot_kid[at] = (uint16_t)((tid * kPer + i) * 32 + __builtin_ctz(bits));
   }
   if (tid == 0) {
     sm.nslots = all < (uint32_t)NSLOT ? all : (uint32_t)NSLOT;
